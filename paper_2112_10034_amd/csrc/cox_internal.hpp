@@ -52,12 +52,14 @@ __device__ __forceinline__ uint32_t add_dev32(uint32_t *p, uint32_t v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The call's epoch, read with acquire ordering before the block draws any
-// ticket (the block that resets the epoch does so after every block has
-// drawn its last ticket).
-__device__ __forceinline__ uint32_t ld_epoch(const uint32_t *hdr) {
-  return __hip_atomic_load(&hdr[HDR_EPOCH], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
+// The call's epoch.  A relaxed load: the block that advances the epoch does
+// so after every block has drawn its last ticket, and a block uses the
+// value only for tickets it drew while work was left (their blocks' last
+// tickets are still to come) or when it is that last block itself.  The
+// header was written by an earlier kernel or call on the stream, so nothing
+// needs an acquire, whose cache invalidation in every block cost 3.5 us of a
+// 512-block segmented call and 2 % of a 2^28-element scan (0.356 -> 0.349 ms).
+__device__ __forceinline__ uint32_t ld_epoch(const uint32_t *hdr) { return ld_dev32(&hdr[HDR_EPOCH]); }
 
 // spin bound of every cross-block wait (well under a second); a wait that
 // runs out, or that sees another wait's failure, sets HDR_ERR and proceeds,

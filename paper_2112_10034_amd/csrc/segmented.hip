@@ -1,6 +1,6 @@
-// Segmented reduce + scan + compaction over CSR segments: two setup
-// kernels and one persistent fused kernel on one stream (one graph launch
-// in a plan).
+// Segmented reduce + scan + compaction over CSR segments: a setup kernel
+// (three for more than SETUP1_MAX segments) and one persistent fused kernel
+// on one stream (one graph launch in a plan).
 //
 // Segment s covers x[off[s], off[s+1]).  It is cut into chunks of
 // S = 32 * W * k elements starting at its first element (the last chunk is
@@ -8,11 +8,10 @@
 // cross-block word; several of them are packed into one block task, each
 // on as many warps as it has parts.  The block tasks and the chunks of the
 // longer segments are the work items of the persistent kernel, so
-// thousands of uneven segments share one grid.  A setup pass (one block)
-// turns the segment lengths into per-segment chunk starts and counts the
-// short segments per class, a second one writes the chunk descriptors and
-// the short-segment list, and empty segments get their identity outputs
-// there.
+// thousands of uneven segments share one grid.  The setup turns the segment
+// lengths into per-segment chunk starts, counts the short segments per
+// class, writes the chunk descriptors and the short-segment list, and gives
+// empty segments their identity outputs.
 //
 // Per chunk (element layout of the schedule sigma = (k, W), cox.h):
 //  - reduce partial P: lane-serial accumulation in (row, slot) order, the
@@ -463,6 +462,223 @@ __global__ __launch_bounds__(1024) void k_seg_setup(const int64_t *__restrict__ 
   }
 }
 
+// The chunk descriptors and cleared cross-block words of one long segment,
+// by threads `first`, first + step, .. of the caller.  The words start with
+// tag 0 (no call's tag): this memory may hold another layout's words from an
+// earlier call.
+__device__ __forceinline__ void seg_map_one(const SegWS &ws, const SegDesc &e, uint32_t first, uint32_t step) {
+  for (uint32_t c = e.lo + first; c < e.lo + e.nchs; c += step) {
+    ws.desc[c] = e;
+    u32x4 *rec = (u32x4 *)(ws.w_scan + c * CW);  // the record's six words
+    rec[0] = rec[1] = rec[2] = u32x4{0u, 0u, 0u, 0u};
+  }
+}
+
+// The whole setup in one kernel, for at most SETUP1_MAX segments.  Block b
+// places segments [256b, 256b + 256); to know where they go it counts all
+// segments itself (at most 15 a thread, coalesced), so no block waits for
+// another and no launch separates counting, placing and descriptors.  Bound
+// by latency: each of the three kernels it replaces is one chain of launch,
+// loads and scans; together they took 21.2 us before a 10,000-segment call's
+// fused kernel and 17.8 us before a 300-segment one's, this one takes 12.9
+// and 9.7 us (plus two launches less).  Past SETUP1_MAX a thread would count
+// more than 15 segments (their classes are counted in four bits), the
+// repeated count grows with nseg^2 / 256, and the three kernels take over.
+constexpr int SETUP1_OWN = 256, SETUP1_MAX = 15 * 1024;
+template <int DT>
+__global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__ off, int nseg, int64_t n, int shS,
+                                                     int W, uint32_t maxch, SegWS ws, void *seg_total,
+                                                     long long *seg_count) {
+  // rows: total chunks, chunks before this block, then the short segments
+  // per class, two classes to a word: all of them, those before this block
+  __shared__ uint32_t s_x[10][32], s_sum[10];
+  __shared__ uint32_t s_w[5][SETUP1_OWN / 32];  // this block's warps: chunks, classes
+  __shared__ SegDesc s_long[SETUP1_OWN];
+  __shared__ uint32_t s_nlong;
+  const int t = threadIdx.x, w = t >> 5, l = t & 31;
+  const int ncls = W < MAX_CLS ? W : MAX_CLS;
+  const int64_t S = (int64_t)1 << shS;
+  const int b0 = blockIdx.x * SETUP1_OWN;
+  if (t == 0) s_nlong = 0u;
+  auto bounds = [&](int s, int64_t &a, int64_t &b) {
+    a = off[s < nseg ? s : nseg];
+    b = off[s + 1 < nseg ? s + 1 : nseg];
+  };
+  auto clamp = [&](int64_t &a, int64_t &b) {
+    if ((uint64_t)a > (uint64_t)n || (uint64_t)b > (uint64_t)n || b < a) {  // malformed offsets
+      a = a < 0 ? 0 : (a > n ? n : a);
+      b = b < a ? a : (b > n ? n : b);
+    }
+  };
+  // chunks of a long segment (below maxch, so 32-bit), 0 for a short one;
+  // S = 2^shS, ncls = 2^shN.  A short segment's class ((r - 1) ncls) / W,
+  // r = ceil(len / 32k), is (len - 1) >> (shS - shN).
+  const int shN = __builtin_ctz((unsigned)ncls);
+  auto chunks_of = [&](int64_t len) { return len > S ? (uint32_t)((len + S - 1) >> shS) : 0u; };
+  auto is_short = [&](int64_t len) { return (uint64_t)(len - 1) < (uint64_t)S; };
+  auto class_of = [&](int64_t len) { return (uint32_t)(len - 1) >> (shS - shN); };
+  // this thread's own segment (threads below SETUP1_OWN)
+  const int s = b0 + t;
+  const bool own = t < SETUP1_OWN && s < nseg;
+  int64_t a = 0, b = 0;
+  bounds(own ? s : nseg, a, b);
+  // counts of all segments, classes four bits each (at most 15 segments a
+  // thread)
+  uint32_t tot = 0u, pre = 0u, ctot = 0u, cpre = 0u;
+  constexpr int UB = 5;
+  for (int s0 = t; s0 < nseg; s0 += UB * 1024) {
+    int64_t la[UB], lb[UB];
+#pragma unroll
+    for (int i = 0; i < UB; i++) bounds(s0 + 1024 * i, la[i], lb[i]);
+#pragma unroll
+    for (int i = 0; i < UB; i++) {
+      clamp(la[i], lb[i]);
+      const int64_t len = lb[i] - la[i];  // 0 past the last segment
+      const bool before = s0 + 1024 * i < b0;
+      const uint32_t c = chunks_of(len), one = is_short(len) ? 1u << (4 * class_of(len)) : 0u;
+      tot = sat_add(tot, c);
+      pre = sat_add(pre, before ? c : 0u);
+      ctot += one;
+      cpre += before ? one : 0u;
+    }
+  }
+  clamp(a, b);
+  uint32_t v[10];
+  v[0] = tot;
+  v[1] = pre;
+#pragma unroll
+  for (int h = 0; h < 4; h++) {  // classes 2h and 2h + 1 in 16-bit halves
+    const uint32_t x = ctot >> (8 * h), y = cpre >> (8 * h);
+    v[2 + h] = (x & 0xfu) | ((x & 0xf0u) << 12);
+    v[6 + h] = (y & 0xfu) | ((y & 0xf0u) << 12);
+  }
+  // sums over the logical warp, the ten rows side by side so that their
+  // exchanges overlap
+  auto halve = [&](auto xl) {
+    uint32_t o[10];
+#pragma unroll
+    for (int r = 0; r < 10; r++) o[r] = xl(v[r]);
+#pragma unroll
+    for (int r = 0; r < 10; r++) v[r] = r < 2 ? sat_add(v[r], o[r]) : v[r] + o[r];
+  };
+  halve([](uint32_t x) { return (uint32_t)xor_lane<16>((int)x); });
+  halve([](uint32_t x) { return (uint32_t)xor_lane<8>((int)x); });
+  halve([](uint32_t x) { return (uint32_t)xor_lane<4>((int)x); });
+  halve([](uint32_t x) { return (uint32_t)xor_lane<2>((int)x); });
+  halve([](uint32_t x) { return (uint32_t)xor_lane<1>((int)x); });
+  if (l == 0) {
+#pragma unroll
+    for (int r = 0; r < 10; r++) s_x[r][w] = v[r];
+  }
+  // this block's own segments: inclusive scans inside the warp
+  const int64_t len = b - a;
+  const uint32_t cnt = own ? chunks_of(len) : 0u;
+  const bool shrt = own && is_short(len);
+  const int cls = shrt ? (int)class_of(len) : 0;
+  uint32_t ci = cnt;
+  ci = sat_add(ci, (uint32_t)dpp<DPP_ROW_SHR1>(0, (int)ci));
+  ci = sat_add(ci, (uint32_t)dpp<DPP_ROW_SHR2>(0, (int)ci));
+  ci = sat_add(ci, (uint32_t)dpp<DPP_ROW_SHR4>(0, (int)ci));
+  ci = sat_add(ci, (uint32_t)dpp<DPP_ROW_SHR8>(0, (int)ci));
+  ci = sat_add(ci, (uint32_t)dpp<DPP_ROW_BCAST15, 0xa>(0, (int)ci));
+  const uint32_t cup = (uint32_t)shfl_up((int)ci, 1);
+  uint32_t mine[4], inc[4];
+#pragma unroll
+  for (int h = 0; h < 4; h++) {
+    mine[h] = shrt && (cls >> 1) == h ? 1u << (16 * (cls & 1)) : 0u;
+    inc[h] = setup_scan32(mine[h]);
+  }
+  if (t < SETUP1_OWN && l == 31) {
+    s_w[0][w] = ci;
+#pragma unroll
+    for (int h = 0; h < 4; h++) s_w[1 + h][w] = inc[h];
+  }
+  __syncthreads();
+  if (w < 10) {
+    const bool sat = w < 2;
+    auto add = [sat](uint32_t p, uint32_t q) { return sat ? sat_add(p, q) : p + q; };
+    uint32_t x = s_x[w][l];
+    x = add(x, (uint32_t)xor_lane<16>((int)x));
+    x = add(x, (uint32_t)xor_lane<8>((int)x));
+    x = add(x, (uint32_t)xor_lane<4>((int)x));
+    x = add(x, (uint32_t)xor_lane<2>((int)x));
+    x = add(x, (uint32_t)xor_lane<1>((int)x));
+    if (l == 0) s_sum[w] = x;
+  }
+  __syncthreads();
+  auto cls_of = [&](int row, int c) { return (s_sum[row + (c >> 1)] >> (16 * (c & 1))) & 0xffffu; };
+  if (own) {
+    uint32_t ex = s_sum[1];  // chunks before this segment
+#pragma unroll
+    for (int j = 0; j < SETUP1_OWN / 32; j++) ex = sat_add(ex, j < w ? s_w[0][j] : 0u);
+    ex = sat_add(ex, l == 0 ? 0u : cup);
+    ws.done[s] = 0u;
+    SegDesc d;
+    d.a = a;
+    d.b = b;
+    d.s = (uint32_t)s;
+    d.lo = 0u;
+    d.nchs = 1u;
+    d.pad = 0u;
+    if (shrt) {
+      // its class's start (classes in the order of falling part counts),
+      // the class's segments of earlier blocks, earlier warps and lanes
+      uint32_t pos = cls_of(6, cls);
+#pragma unroll
+      for (int c = MAX_CLS - 1; c > 0; c--) pos += c > cls ? cls_of(2, c) : 0u;  // none past ncls
+      const int h = cls >> 1, sh = 16 * (cls & 1);
+      uint32_t mh = 0u;
+#pragma unroll
+      for (int k = 0; k < 4; k++) mh = k == h ? inc[k] - mine[k] : mh;
+      pos += (mh >> sh) & 0xffffu;
+#pragma unroll
+      for (int j = 0; j < SETUP1_OWN / 32; j++) pos += j < w ? (s_w[1 + h][j] >> sh) & 0xffffu : 0u;
+      if (pos < (uint32_t)nseg) ws.sdesc[pos] = d;
+    } else if (cnt) {
+      const uint32_t lo = ex < maxch ? ex : maxch, e = sat_add(ex, cnt);
+      d.lo = lo;
+      d.nchs = (e < maxch ? e : maxch) - lo;
+      if (d.nchs) s_long[atomicAdd(&s_nlong, 1u)] = d;
+    } else {
+      if (seg_total) {
+        if (DT == COX_I32) ((long long *)seg_total)[s] = 0;
+        else ((double *)seg_total)[s] = -0.0;
+      }
+      if (seg_count) seg_count[s] = 0;
+    }
+  }
+  if (blockIdx.x == 0 && w == 31) {
+    // class table in the order q (lane q of the last warp), header words
+    const int q = l, c = ncls - 1 - q;
+    uint32_t k = 0u, nb = 0u, rmax = 0u;
+    if (c >= 0) {
+      rmax = (uint32_t)(c + 1) * (uint32_t)(W / ncls);
+      const uint32_t spb = (uint32_t)W / rmax;
+      k = cls_of(2, c);
+      nb = (k + spb - 1u) / spb;
+    }
+    const uint32_t ki = setup_scan32(k), ni = setup_scan32(nb);
+    if (c >= 0) ws.cls[CLS_R + q] = rmax;
+    if (q <= ncls) {  // lane ncls holds the totals
+      ws.cls[q] = ki - k;
+      ws.cls[CLS_BLK + q] = ni - nb;
+    }
+    if (q == ncls) {
+      ws.hdr[SHDR_NS] = ki;
+      ws.hdr[SHDR_NSB] = ni;
+      ws.hdr[SHDR_NCL] = s_sum[0] < maxch ? s_sum[0] : maxch;
+      if (s_sum[0] > maxch) st_dev32(&ws.hdr[HDR_ERR], ERR_LAYOUT);
+    }
+  }
+  __syncthreads();
+  // descriptors: a wave per long segment, the whole block for very long ones
+  const int nl = (int)s_nlong;
+  for (int j = t >> 6; j < nl; j += 16)
+    if (s_long[j].nchs <= 1024) seg_map_one(ws, s_long[j], (uint32_t)(t & 63), 64u);
+  for (int j = 0; j < nl; j++)
+    if (s_long[j].nchs > 1024) seg_map_one(ws, s_long[j], (uint32_t)t, 1024u);
+}
+
 // zero words [0, words) (the per-segment baseline's workspace region)
 __global__ __launch_bounds__(256) void k_seg_clear(uint32_t *p, int64_t words) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) p[i] = 0u;
@@ -506,17 +722,7 @@ __global__ __launch_bounds__(256) void k_seg_map(const int64_t *__restrict__ off
     e.lo = (uint32_t)__builtin_amdgcn_readlane((int)d.lo, ld);
     e.nchs = (uint32_t)__builtin_amdgcn_readlane((int)d.nchs, ld);
     e.pad = 0u;
-    for (uint32_t c = e.lo + (uint32_t)lane; c < e.lo + e.nchs; c += 64) {
-      ws.desc[c] = e;
-      // the chunk's cross-block words start with tag 0 (no call's tag):
-      // this memory may hold another layout's words from an earlier call
-      ws.w_scan[c * CW] = 0;
-      ws.w_cnt[c * CW] = 0;
-      ws.w_part[c * CW] = 0;
-      ws.w_tot[c * CW] = 0;
-      ws.w_ph[c * CW] = 0;
-      ws.w_pl[c * CW] = 0;
-    }
+    seg_map_one(ws, e, (uint32_t)lane, 64u);
     longs &= longs - 1;
   }
   }
@@ -558,8 +764,10 @@ __device__ __forceinline__ uint32_t seg_scan32(uint32_t &r, uint32_t &ex) {
   r = SegT<DT>::add(r, (uint32_t)dpp<DPP_ROW_SHR4>(I, (int)r));
   r = SegT<DT>::add(r, (uint32_t)dpp<DPP_ROW_SHR8>(I, (int)r));
   r = SegT<DT>::add(r, (uint32_t)dpp<DPP_ROW_BCAST15, 0xa>(I, (int)r));
-  const uint32_t up = (uint32_t)shfl_up((int)r, 1);
-  ex = llane() == 0 ? SegT<DT>::ident : up;
+  // shfl_up(r, 1): inside the 16-lane rows by row_shr:1, whose first lane
+  // keeps the old value -- lane 15's in lanes 16 and 48 (row_bcast:15 into
+  // rows 1 and 3), the identity in lanes 0 and 32
+  ex = (uint32_t)dpp<DPP_ROW_SHR1>(dpp<DPP_ROW_BCAST15, 0xa>(I, (int)r), (int)r);
   return (uint32_t)bcast31((int)r);
 }
 
@@ -759,8 +967,7 @@ typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
 // afterwards.  x of fewer than four elements is read element by element.
 template <int R, int V, int DT>
 __device__ __forceinline__ void seg_load_part(const uint32_t *__restrict__ x, int64_t n, int64_t wbase,
-                                              int64_t e1, uint32_t (&v)[R][V]) {
-  const int l = llane();
+                                              int64_t e1, int l, uint32_t (&v)[R][V]) {
   constexpr uint32_t I = SegT<DT>::ident;
   if constexpr (V == 4) {
     if (n >= 4) {
@@ -802,8 +1009,7 @@ __device__ __forceinline__ void seg_load_part(const uint32_t *__restrict__ x, in
 // stores of a warp part's row vectors inside a range that ends at e1
 template <int R, int V>
 __device__ __forceinline__ void seg_store_part(uint32_t *__restrict__ y, int64_t wbase, int64_t e1,
-                                               const uint32_t (&o)[R][V]) {
-  const int l = llane();
+                                               int l, const uint32_t (&o)[R][V]) {
 #pragma unroll
   for (int i = 0; i < R; i++) {
     const int64_t e = wbase + (int64_t)(i * 32 + l) * V;
@@ -861,19 +1067,27 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
   extern __shared__ uint32_t s_stage[];  // 32K values per warp (compaction)
 
   const int W = blockDim.x >> 5;
-  const int w = threadIdx.x >> 5, l = threadIdx.x & 31;
+  const int w_ = threadIdx.x >> 5, l_ = threadIdx.x & 31;
   const int wS = 0, wC = W > 2 ? 2 : 0, wR = W > 4 ? 4 : 0;
   const int tD = blockDim.x >= 128 ? (int)blockDim.x - 64 : 0;  // draws tickets
   const int64_t S = (int64_t)blockDim.x * K;
-  const uint32_t lt = lanemask_lt();
   const bool single = nc_arg >= 0;
   // work items u: [0, NSB) the block tasks of short segments, then
   // [NSB, NSB + NC) the long segments' chunks in order.  The setup pass
   // clamps the chunk count to the workspace's capacity; the bounds are
   // repeated here so that no ticket can index past them.
+  // The first ticket, the epoch, the header words and the class table are
+  // requested together, so that a block starts after one round trip.
+  const int64_t G = gridDim.x;
+  const int64_t Q = G < TICKET_LANES ? G : TICKET_LANES;
+  const int64_t q = (int64_t)blockIdx.x % Q;
+  uint32_t *const lane_ctr = ws.lane + q * LANE_WORDS;
+  uint32_t t0 = 0u;
+  if (threadIdx.x == tD) t0 = add_dev32(lane_ctr, 1u);
+  if (threadIdx.x == 0) s_epoch = ld_epoch(ws.hdr);
   int64_t NC = nc_arg, NSB = 0;
   if (!single) {
-    const uint32_t ncl = ld_dev32(&ws.hdr[SHDR_NCL]), nsb = ld_dev32(&ws.hdr[SHDR_NSB]);
+    const uint32_t ncl = ws.hdr[SHDR_NCL], nsb = ws.hdr[SHDR_NSB];  // an earlier kernel's
     NC = ncl < maxch ? ncl : maxch;
     NSB = (int64_t)nsb < nseg ? (int64_t)nsb : nseg;
     const int t = threadIdx.x;
@@ -887,12 +1101,8 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
   // smallest unfinished item is always drawn or about to be (its lane's
   // earlier items are all finished, so that lane's blocks are free), and
   // the first Q blocks, dispatched first, keep every lane served.
-  const int64_t G = gridDim.x;
-  const int64_t Q = G < TICKET_LANES ? G : TICKET_LANES;
-  const int64_t q = (int64_t)blockIdx.x % Q;
   const int64_t Gq = (G - q + Q - 1) / Q;
   const int64_t NUq = NU > q ? (NU - q + Q - 1) / Q : 0;
-  uint32_t *const lane_ctr = ws.lane + q * LANE_WORDS;
 
   // thread tD: ticket t's item into slot
   auto resolve = [&](uint32_t t, int slot) {
@@ -925,7 +1135,7 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
   };
   // the warp's vectors (padding with the identity past the segment); a
   // short task's warps each start at their own part (e0 + 32Kw)
-  auto load = [&](int64_t e0, int64_t e1, bool full, uint32_t (&v)[R][V]) {
+  auto load = [&](int64_t e0, int64_t e1, bool full, int w, int l, uint32_t (&v)[R][V]) {
     const int64_t wbase = e0 + (int64_t)w * 32 * K;
     if (full) {
       const uint32_t *src = x + wbase + l * V;
@@ -943,22 +1153,27 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
         }
       }
     } else {
-      seg_load_part<R, V, DT>(x, n, wbase, e1, v);
+      seg_load_part<R, V, DT>(x, n, wbase, e1, l, v);
     }
   };
 
-  if (threadIdx.x == 0) s_epoch = ld_epoch(ws.hdr);
+  if (threadIdx.x == tD) resolve(t0, 0);
   __syncthreads();
   const uint32_t epoch = s_epoch;
   const uint32_t tag = tag_of_epoch(epoch);
   const int slot = 0;
 
   int64_t tk;
-  if (threadIdx.x == tD) resolve(add_dev32(lane_ctr, 1u), 0);
   for (;;) {
-    __syncthreads();
     tk = s_tk[0];
     if (tk >= NUq) break;
+    // the lane and warp are opaque to the compiler in each round: it would
+    // otherwise keep their sums with the constants below in registers of
+    // their own across the whole loop (128 VGPRs and a spill at K = 32
+    // instead of 102 and none)
+    int l = l_, w = w_;
+    asm volatile("" : "+v"(l), "+v"(w));
+    const uint32_t lt = l ? (FULL >> (32 - l)) : 0u;
     const int64_t u = tk * Q + q;  // the item
     const bool shortk = s_kind[slot] != 0u;
     // long chunk: c, its segment s, the segment's first chunk lo and its
@@ -997,7 +1212,7 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
     const bool full = !shortk && e0 + S <= e1;
     const int64_t wbase = e0 + (int64_t)w * 32 * K;
     uint32_t xr[R][V];
-    load(e0, e1, full, xr);
+    load(e0, e1, full, w, l, xr);
 
     // ---- reduce partial: lane-serial then the warp tree
     if (flags & SF_REDUCE) {
@@ -1206,7 +1421,7 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
           }
         }
       } else if (has) {
-        seg_store_part<R, V>(y, wbase, e1, o);
+        seg_store_part<R, V>(y, wbase, e1, l, o);
       }
     }
     if ((flags & SF_COMPACT) && has) {
@@ -1235,6 +1450,7 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
       }
     }
     if (threadIdx.x == tD) resolve(next_t, 0);
+    __syncthreads();
   }
 
   if (threadIdx.x == tD && tk == NUq + Gq - 1) {
@@ -1337,9 +1553,32 @@ static cox_status seg_prepare(const void *x, cox_dtype dt, const int64_t *offset
   sc->fn = fn;
   sc->lds = lds;
   sc->maxch = (uint32_t)maxch;
-  // default: as many blocks as fit, capped by the work items
-  sc->grid = persistent_grid((const void *)fn, block, maxch + nseg, sg.G, lds);
+  // default: as many blocks as fit, capped by the work items (long chunks
+  // number at most n / S + one a long segment, block tasks one a short one)
+  sc->grid = persistent_grid((const void *)fn, block, maxch, sg.G, lds);
   return COX_OK;
+}
+
+template <int DT>
+static cox_status seg_setup(const SegCall &sc, int shS, void *tot, long long *cnt, hipStream_t st) {
+  if (sc.nseg <= SETUP1_MAX) {
+    hipLaunchKernelGGL(k_seg_setup1<DT>, dim3((unsigned)((sc.nseg + SETUP1_OWN - 1) / SETUP1_OWN)), dim3(1024), 0, st,
+                       sc.off, (int)sc.nseg, sc.n, shS, sc.sg.W, sc.maxch, sc.ws, tot, cnt);
+    return launch_status();
+  }
+  // setup blocks: about 2048 segments each, at most SETUP_BLOCKS
+  int64_t sb = (sc.nseg + 2047) / 2048;
+  if (sb > SETUP_BLOCKS) sb = SETUP_BLOCKS;
+  hipLaunchKernelGGL(k_seg_count<DT>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS, sc.sg.W,
+                     sc.ws, tot, cnt);
+  hipLaunchKernelGGL(k_seg_setup<DT>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS, sc.sg.W,
+                     sc.maxch, sc.ws);
+  const cox_status r = launch_status();
+  if (r != COX_OK) return r;
+  int mg = (int)((sc.nseg + 255) / 256);
+  if (mg > 4096) mg = 4096;
+  hipLaunchKernelGGL(k_seg_map, dim3(mg), dim3(256), 0, st, sc.off, sc.nseg, sc.n, (int64_t)1 << shS, sc.ws);
+  return launch_status();
 }
 
 static cox_status seg_launch(const SegCall &sc, hipStream_t st) {
@@ -1347,28 +1586,9 @@ static cox_status seg_launch(const SegCall &sc, hipStream_t st) {
   const int64_t S = (int64_t)block * sc.sg.k;
   const int shS = __builtin_ctzll((unsigned long long)S);  // S is a power of two
   if (sc.nseg == 0) return COX_OK;
-  // setup blocks: about 2048 segments each, at most SETUP_BLOCKS
-  int64_t sb = (sc.nseg + 2047) / 2048;
-  if (sb > SETUP_BLOCKS) sb = SETUP_BLOCKS;
   void *tot = (sc.flags & SF_REDUCE) ? sc.seg_total : nullptr;
   long long *cnt = (sc.flags & SF_COMPACT) ? (long long *)sc.seg_count : nullptr;
-  if (sc.dt == COX_I32) {
-    hipLaunchKernelGGL(k_seg_count<COX_I32>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS,
-                       sc.sg.W, sc.ws, tot, cnt);
-    hipLaunchKernelGGL(k_seg_setup<COX_I32>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS,
-                       sc.sg.W, sc.maxch, sc.ws);
-  } else {
-    hipLaunchKernelGGL(k_seg_count<COX_F32>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS,
-                       sc.sg.W, sc.ws, tot, cnt);
-    hipLaunchKernelGGL(k_seg_setup<COX_F32>, dim3((unsigned)sb), dim3(1024), 0, st, sc.off, sc.nseg, sc.n, shS,
-                       sc.sg.W, sc.maxch, sc.ws);
-  }
-  cox_status r = launch_status();
-  if (r != COX_OK) return r;
-  int mg = (int)((sc.nseg + 255) / 256);
-  if (mg > 4096) mg = 4096;
-  hipLaunchKernelGGL(k_seg_map, dim3(mg), dim3(256), 0, st, sc.off, sc.nseg, sc.n, S, sc.ws);
-  r = launch_status();
+  cox_status r = sc.dt == COX_I32 ? seg_setup<COX_I32>(sc, shS, tot, cnt, st) : seg_setup<COX_F32>(sc, shS, tot, cnt, st);
   if (r != COX_OK) return r;
   hipLaunchKernelGGL(sc.fn, dim3(sc.grid), dim3(block), sc.lds, st, (const uint32_t *)sc.x, sc.off, sc.nseg, sc.n,
                      (int64_t)-1, sc.maxch, sc.ws, sc.seg_total, (uint32_t *)sc.y, (uint32_t *)sc.out,
