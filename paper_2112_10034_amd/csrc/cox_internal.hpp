@@ -52,6 +52,9 @@ __device__ __forceinline__ uint32_t add_dev32(uint32_t *p, uint32_t v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// waits until the wave's own stores have completed
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // The call's epoch.  A relaxed load: the block that advances the epoch does
 // so after every block has drawn its last ticket, and a block uses the
 // value only for tickets it drew while work was left (their blocks' last

@@ -69,7 +69,6 @@ __device__ __forceinline__ double ldcd(const double *p) {
 __device__ __forceinline__ void stcd(double *p, double v) {
   __hip_atomic_store((uint64_t *)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Every block of the (co-resident) grid calls this with every thread; the
 // device-coherent writes of all blocks before it are visible to the

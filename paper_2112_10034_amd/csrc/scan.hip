@@ -29,6 +29,8 @@
 // have finished) resets the counter and advances the epoch whose tag marks
 // this call's status words, so the workspace needs no clearing between
 // calls.  Every wait is bounded (MAX_SPIN); running out sets HDR_ERR.
+//
+// Short inputs under the default schedule take k_once instead (below).
 #include <mutex>
 
 #include "cox_internal.hpp"
@@ -328,6 +330,281 @@ __global__ __launch_bounds__(1024) void k_lookback(const int32_t *__restrict__ x
   }
 }
 
+// ---------------------------------------------------------------- short inputs
+// One pass, one chunk per block, for inputs of at most ONCE_CHUNKS chunks
+// (default schedule only; the result does not depend on it).  What bounds a
+// short call of k_lookback is its chain of round trips: epoch, ticket (11.5
+// ns each, one after another), loads, look-back windows of 32 chunks, and
+// with chunks of 32768 elements most of the chip idle.  Here block b is chunk
+// b, chunks are small enough to spread over the chip, and every block reads
+// the aggregates of all chunks before it at once: one exchange instead of a
+// chain.  Time per call in a graph of calls (empty kernel 2.5 us): scan of
+// 1000 / 65,613 / 1,000,003 / 4,194,304 elements 3.2 / 4.4 / 5.9 / 8.0 us, with
+// k_lookback 5.6 / 6.9 / 12.8 / 12.6 us; compaction 3.4 / 4.8 / 6.3 / 8.8
+// us, 7.2 / 8.6 / 11.0 / 13.9.
+//
+// No ticket orders the blocks, so a block may wait for one that the device
+// has not started.  After ONCE_SPINS polls it therefore adds up the missing
+// chunk from x itself (nothing writes x: the output lies apart), so every
+// block ends whatever order the blocks start in, also beside other kernels.
+// The last chunk's block advances the epoch once it has seen every other
+// block's own word: each was published by a block that has read the epoch.
+// Only that one block may wait for blocks not yet started.  (Counting the
+// started blocks with an atomic instead cost 2.4 us at 245 blocks.)
+constexpr int ONCE_CHUNKS = 1024;
+constexpr uint32_t ONCE_SPINS = 512;  // some hundred microseconds
+
+// inclusive scan of v over the 64 lanes of the wave
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v = warp_incl_scan_u32(v);
+  // lane 31's value into lanes 32 .. 63 (rows 2 and 3)
+  v += (uint32_t)dpp<0x143, 0xc>(0, (int)v);  // row_bcast:31
+  return v;
+}
+
+template <int K, int BT, int MODE>
+__global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *__restrict__ x, int32_t *__restrict__ out,
+                                             long long *__restrict__ count, int64_t n, int nch,
+                                             uint64_t *__restrict__ status, uint32_t *__restrict__ hdr) {
+  static_assert(K % 4 == 0, "rows of 16-byte vectors");
+  constexpr int R = K / 4, NW = BT / 64, S = BT * K;
+  __shared__ uint32_t s_w[NW], s_pre[NW], s_epoch, s_miss, s_late;
+  __shared__ int32_t s_stage[MODE == MODE_COMPACT ? S + NW * 64 : 1];
+  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
+  const int c = blockIdx.x;
+  uint32_t e = 0u;
+  if (t == 0 && nch > 1) {
+    e = ld_epoch(hdr);
+    s_miss = 0u;
+  }
+  // the wave's rows of 256 elements; past n every lane rereads the last one
+  const int64_t wbase = (int64_t)c * S + wv * (64 * K);
+  const bool full = (int64_t)(c + 1) * S <= n;
+  uint32_t v[R][4];
+  if (full) {
+    const int32_t *src = x + wbase + lane * 4;
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const u32x4 q = ld_stream4(src + i * 256);
+      v[i][0] = q.x; v[i][1] = q.y; v[i][2] = q.z; v[i][3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int64_t p = wbase + i * 256 + lane * 4 + j;
+        v[i][j] = ld_stream1(x + (p < n ? p : n - 1));
+      }
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+        if (wbase + i * 256 + lane * 4 + j >= n) v[i][j] = 0u;
+  }
+  if (t == 0 && nch > 1) {
+    s_epoch = e;
+  }
+  uint32_t wsum = 0u;  // wave-uniform: the rows before, then the wave's total
+  int32_t *region = s_stage + (MODE == MODE_COMPACT ? wv * (64 * K + 64) : 0);
+  if constexpr (MODE == MODE_SCAN) {
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+#pragma unroll
+      for (int j = 1; j < 4; j++) v[i][j] += v[i][j - 1];
+      const uint32_t r = v[i][3], incl = wave_incl_scan_u32(r), add = wsum + (incl - r);
+#pragma unroll
+      for (int j = 0; j < 4; j++) v[i][j] += add;
+      wsum += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+  } else {
+    // kept elements to their rank in the wave's region, the others to the
+    // lane's trash slot after it
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      uint32_t pos = wsum, cnt = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const uint64_t B = __builtin_amdgcn_ballot_w64((int32_t)v[i][j] > 0);
+        pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(B >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)B, pos));
+        cnt += (uint32_t)__builtin_popcountll(B);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const bool k = (int32_t)v[i][j] > 0;
+        region[k ? pos : (uint32_t)(64 * K + lane)] = (int32_t)v[i][j];
+        pos += k ? 1u : 0u;
+      }
+      wsum += cnt;
+    }
+  }
+  if (lane == 0) s_w[wv] = wsum;
+  __syncthreads();
+  uint32_t off = 0u, agg = 0u;  // the waves before this one, the block's total
+#pragma unroll
+  for (int j = 0; j < NW; j++) {
+    const uint32_t u = s_w[j];
+    off += j < wv ? u : 0u;
+    agg += u;
+  }
+  uint32_t pre = 0u;
+  if (nch > 1) {
+    const uint32_t tag = tag_of_epoch(s_epoch);
+    if (t == 0) st_dev(&status[c], st_pack(tag, ST_AGG, agg));
+    // thread t: the aggregates of chunks t, t + BT, .. below c
+    constexpr int NP = (ONCE_CHUNKS + BT - 1) / BT;
+    uint64_t w[NP];
+#pragma unroll
+    for (int k = 0; k < NP; k++) w[k] = t + k * BT < c ? ld_dev(&status[t + k * BT]) : st_pack(tag, ST_AGG, 0u);
+    bool late = false;
+#pragma unroll
+    for (int k = 0; k < NP; k++) {
+      uint32_t spins = 0;
+      while (st_tag(w[k]) != tag && ++spins < ONCE_SPINS) {
+        __builtin_amdgcn_s_sleep(1);
+        w[k] = ld_dev(&status[t + k * BT]);
+      }
+      late = late || st_tag(w[k]) != tag;
+    }
+    if (late) s_miss = 1u;
+    auto sum_words = [&]() {
+      uint32_t sum = 0u;
+#pragma unroll
+      for (int k = 0; k < NP; k++) sum += st_val(w[k]);
+      sum = wave_incl_scan_u32(sum);
+      if (lane == 63) s_pre[wv] = sum;
+    };
+    sum_words();
+    __syncthreads();
+    if (s_miss) {
+      // some block before this one has not published: its chunk is added up
+      // here, by the whole block (all chunks before c are full)
+      for (int p = 0; p < c; p++) {
+        const int k0 = p / BT;
+        if (t == p % BT) {
+          s_late = 0u;
+#pragma unroll
+          for (int k = 0; k < NP; k++)
+            if (k == k0) s_late = st_tag(w[k]) != tag ? 1u : 0u;
+        }
+        __syncthreads();
+        if (s_late) {  // uniform: written before the barrier, next after the one below
+          uint32_t a = 0u;
+          for (int i = t; i < S; i += BT) {
+            const int32_t xv = x[(int64_t)p * S + i];
+            a += MODE == MODE_SCAN ? (uint32_t)xv : (xv > 0 ? 1u : 0u);
+          }
+          a = wave_incl_scan_u32(a);
+          if (lane == 63) s_w[wv] = a;
+          __syncthreads();
+          if (t == p % BT) {
+            a = 0u;
+            for (int j = 0; j < NW; j++) a += s_w[j];
+#pragma unroll
+            for (int k = 0; k < NP; k++)
+              if (k == k0) w[k] = st_pack(tag, ST_AGG, a);
+          }
+        }
+        __syncthreads();
+      }
+      sum_words();
+      if (c == nch - 1 && late) {
+        // the epoch may move on only when these blocks have read it
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+          uint32_t spins = 0;
+          while (t + k * BT < c && st_tag(ld_dev(&status[t + k * BT])) != tag) {
+            if (++spins >= MAX_SPIN) {
+              st_dev32(&hdr[HDR_ERR], tag);
+              break;
+            }
+            __builtin_amdgcn_s_sleep(8);
+          }
+        }
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < NW; j++) pre += s_pre[j];
+    if (c == nch - 1 && t == 0) st_dev32(&hdr[HDR_EPOCH], s_epoch + 1u);
+  }
+  const uint32_t at = pre + off;
+  if constexpr (MODE == MODE_SCAN) {
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const int64_t p = wbase + i * 256 + lane * 4;
+      if (full) {
+        st_stream4(out + p, v[i][0] + at, v[i][1] + at, v[i][2] + at, v[i][3] + at);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+          if (p + j < n) out[p + j] = (int32_t)(v[i][j] + at);
+      }
+    }
+  } else {
+    if (c == nch - 1 && t == 0) *count = (long long)pre + (long long)agg;
+    // the wave's run in 16-byte vectors aligned in global memory, its ragged
+    // first and last elements by lanes 0 .. 3 and 4 .. 7
+    int32_t *dst = out + at;
+    const uint32_t h0 = (uint32_t)(-(uintptr_t)dst >> 2) & 3u, hn = h0 < wsum ? h0 : wsum;
+    const uint32_t nv = (wsum - hn) >> 2, tn = (wsum - hn) & 3u, l = (uint32_t)lane;
+    for (uint32_t k = l; k < nv; k += 64u) *(u32x4 *)(dst + hn + 4u * k) = *(const u32x4u *)(region + hn + 4u * k);
+    const uint32_t si = l < 4u ? l : hn + 4u * nv + (l - 4u);
+    if (l < 4u ? l < hn : l - 4u < tn) dst[si] = region[si];
+  }
+}
+
+using once_fn = void (*)(const int32_t *, int32_t *, long long *, int64_t, int, uint64_t *, uint32_t *);
+
+// The kernel for n elements, by measurement (us per call, scan / compaction):
+//  - up to 2^18 elements 8192 a block with 1024 threads, 8 a lane: fewest
+//    blocks to read from (131,072: 4.5 / 4.9; 1024-element chunks 5.5 / 5.7);
+//  - then 8192 with 512 threads, 16 a lane (1,000,003: 6.0 / 6.5, 4096-element
+//    chunks 6.4 / 6.5; 2^22: 8.4 / 8.7, 16384-element chunks 11.4 / 8.9), for
+//    compaction up to 2^22, for scans up to 2^23 (17.2; k_lookback 19.3);
+//  - compaction goes on with 16384 a block up to 2^24 (2^23: 12.7, with 8192
+//    15.4, k_lookback 17.9; 2^24: 26.7, k_lookback 28.0).
+// Past that the aggregates that every block reads (the square of the blocks)
+// cost more than the tickets and windows of k_lookback.
+struct OncePick {
+  once_fn fn;
+  int S, BT;
+};
+template <int MODE>
+static OncePick pick_once(int64_t n) {
+  if (n <= 1 << 18) return {k_once<8, 1024, MODE>, 8192, 1024};
+  if (n <= (MODE == MODE_SCAN ? 1 << 23 : 1 << 22)) return {k_once<16, 512, MODE>, 8192, 512};
+  if constexpr (MODE == MODE_COMPACT)
+    if (n <= 1 << 24) return {k_once<16, 1024, MODE>, 16384, 1024};
+  return {nullptr, 0, 0};
+}
+
+static bool default_schedule(const cox_cfg *cfg) {
+  return !cfg || (!cfg->items_per_lane && !cfg->warps_per_block && !cfg->grid_blocks);
+}
+
+static bool disjoint(const void *a, const void *b, size_t bytes) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return p + bytes <= q || q + bytes <= p;
+}
+
+// Launches the short-input kernel if it applies (default schedule, few
+// enough chunks, separate buffers, room for the words -- what k_lookback
+// asks for always has it); false if not.
+template <int MODE>
+static bool launch_once(const int32_t *x, int32_t *out, long long *count, int64_t n, const cox_cfg *cfg, void *ws,
+                        size_t ws_bytes, hipStream_t st, cox_status *r) {
+  if (n <= 0 || !default_schedule(cfg) || !disjoint(x, out, (size_t)n * 4)) return false;
+  const OncePick p = pick_once<MODE>(n);
+  if (!p.fn) return false;
+  const int64_t nch = (n + p.S - 1) / p.S;
+  if (nch > ONCE_CHUNKS || ws_bytes < WS_HEADER + 8 * (size_t)nch) return false;
+  hipLaunchKernelGGL(p.fn, dim3((unsigned)nch), dim3(p.BT), 0, st, x, out, count, n, (int)nch,
+                     (uint64_t *)((char *)ws + WS_HEADER), (uint32_t *)ws);
+  *r = launch_status();
+  return true;
+}
+
 using lb_fn = void (*)(const int32_t *, int32_t *, long long *, int64_t, int64_t, uint64_t *, int64_t,
                        uint32_t *);
 
@@ -436,6 +713,7 @@ cox_status cox_warp_scan(const int32_t *x, int32_t *y, int64_t n, const cox_cfg 
   if (n == 0) return COX_OK;
   if (!y) return COX_ERR_INVALID;
   if (!aligned16(y)) return COX_ERR_ALIGN;
+  if (launch_once<MODE_SCAN>(x, y, nullptr, n, cfg, ws, ws_bytes, (hipStream_t)stream, &st)) return st;
   lb_fn fn = pick_lb<MODE_SCAN>(sg.k);
   if (!fn) return COX_ERR_UNSUPPORTED;
   const int block = 32 * sg.W;
@@ -462,7 +740,9 @@ cox_status cox_warp_scan_noalloc(const int32_t *x, int32_t *y, int64_t n, const 
   void *ws = nullptr;
   st = scratch_for_device(hs, &ws);
   if (st != COX_OK) return st;
-  if (n > 0) {
+  if (launch_once<MODE_SCAN>(x, y, nullptr, n, cfg, ws, SCRATCH_BYTES, hs, &st)) {
+    if (st != COX_OK) return st;
+  } else if (n > 0) {
     const int block = 32 * sg.W;
     const int grid = persistent_grid((const void *)fn, block, nch, sg.G);
     hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, hs, x, y, (long long *)nullptr, n, nch,
@@ -484,6 +764,7 @@ cox_status cox_ballot_compact(const int32_t *x, int64_t n, int32_t *out, int64_t
   cox_status st = check_lookback_call(COX_OP_COMPACT, n, x, cfg, ws, ws_bytes, &sg, &nch);
   if (st != COX_OK) return st;
   if (!count || (n > 0 && !out)) return COX_ERR_INVALID;
+  if (launch_once<MODE_COMPACT>(x, out, (long long *)count, n, cfg, ws, ws_bytes, (hipStream_t)stream, &st)) return st;
   lb_fn fn = pick_lb<MODE_COMPACT>(sg.k);
   if (!fn) return COX_ERR_UNSUPPORTED;
   const int block = 32 * sg.W;
