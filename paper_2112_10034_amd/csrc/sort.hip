@@ -15,8 +15,10 @@
 //     row_half_mirror exchanges);
 //   - partner in the other half of the wave (a group of 64 lanes, the
 //     full-wave sort): the in-half exchange, then v_permlane32_swap;
-//   - partner in another wave (groups wider than a wave, the multi-warp
-//     sort): through shared memory, between two block barriers.
+//   - partner in another wave (one key per lane, groups wider than a wave):
+//     through shared memory, between two block barriers.
+// Groups of 128 .. 1024 keys at the default 4 keys per lane are sorted by
+// k_group_sort instead (below): 32 keys per lane, a group inside one wave.
 // The layers inside one lane's K registers (every merge size up to K) are
 // replaced by Batcher's odd-even merge sort of the K registers, which needs
 // fewer comparators.  The sorted result is the unique ascending order, so
@@ -177,20 +179,27 @@ __device__ __forceinline__ void store_keys(uint32_t *__restrict__ p, const uint3
 }
 
 // keys of one round: U rows of 256 lane vectors starting at lane vector
-// vbase (row u = vectors vbase + 256u); a round that runs past n loads
-// element by element and pads with the maximum key
+// vbase (row u = vectors vbase + 256u).  In a round that runs past n the
+// vectors past the last whole one read vector 0 instead, so that every load
+// is unconditional and all are in flight together (element by element, each
+// waited for, such a round took 1.5 us of a call on 2^22 + 17 keys); they
+// become the maximum key, and the partial vector is read element by element
 template <int K, int U>
 __device__ __forceinline__ void load_round(const uint32_t *keys, int64_t vbase, int64_t n, bool full,
                                            uint32_t (&key)[U][K]) {
-  if (full) {
+  const int64_t nv = full ? vbase + 256 * U : n / K;  // vectors below nv are whole
+  if (nv > 0) {
 #pragma unroll
-    for (int u = 0; u < U; u++) load_keys<K>(keys + (vbase + 256 * u) * K, key[u]);
-  } else {
+    for (int u = 0; u < U; u++) load_keys<K>(keys + (vbase + 256 * u < nv ? vbase + 256 * u : 0) * K, key[u]);
+  }
+  if (!full) {
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const int64_t e0 = (vbase + 256 * u) * K;
+      const int64_t v = vbase + 256 * u;
+      if (v >= nv) {
 #pragma unroll
-      for (int r = 0; r < K; r++) key[u][r] = e0 + r < n ? keys[e0 + r] : 0xffffffffu;
+        for (int r = 0; r < K; r++) key[u][r] = v == nv && v * K + r < n ? keys[v * K + r] : 0xffffffffu;
+      }
     }
   }
 }
@@ -243,6 +252,192 @@ __global__ __launch_bounds__(256) void k_tile_sort(const uint32_t *keys, uint32_
     load_round<K, U>(keys, vbase, n, full, key);
     sort_group<K, T, U>(key, g, lds);
     store_round<K, U>(out, vbase, n, full, key);
+  }
+}
+
+// ---------------------------------------------------------------- wide groups
+// Groups of T = 128 .. 1024 keys, 32 keys per lane: LG = T / 32 lanes hold a
+// group, a wave 2048 keys, and no block barrier is needed.
+//
+// What bounds it: VALU issue.  A compare-exchange inside a lane costs one
+// operation per key, one across lanes two (the exchange and the median), so
+// layers are run inside lanes where possible.  In layout A lane l of a group
+// holds the keys 32l .. 32l + 31 (index bits 4 .. 0 in the register number);
+// in layout B the register number holds the index bits from 5 up, and lane l
+// the low bits.  The merge of 2^m keys runs its layers for bits m - 1 .. 5
+// across lanes by DPP (m <= 7) or in layout B (m >= 8), the others in layout
+// A; shared memory turns one layout into the other, 8 vector and 32 word
+// accesses a lane, on a pipe of its own.  At T = 1024 that is 55 operations
+// per key and 7 turns instead of 77 operations, three block barriers and
+// exchanges of every key through shared memory (4 keys per lane, 4 waves per
+// group).  2^26 keys in groups of 128 / 256 / 512 / 1024: 95.7 / 95.3 / 112 /
+// 129 us against 99 / 119 / 152 / 175 us, the first two at the rate of a plain
+// copy.
+//
+// The network is the bitonic sorter with directions: blocks of 2^m keys are
+// sorted alternately up and down (bit m of the index), the last merge up.
+// med3(a, b, 0) is the minimum and med3(a, b, ~0) the maximum, so a
+// direction that differs between lanes is a mask operand.
+constexpr int GROW = 36;  // words of a lane's row in shared memory: 16-byte rows, all banks
+template <int T>
+struct GroupLds {
+  static constexpr int LG = T / 32, GPW = 64 / LG;
+  // words of a group; the padding spreads the groups of a wave over the
+  // banks when each lane reads its words of layout B
+  static constexpr int GS = LG * GROW + (LG == 32 ? 32 : LG == 16 ? 16 : LG == 8 ? 8 : 4);
+};
+
+__device__ __forceinline__ void cx_dir(uint32_t &a, uint32_t &b, uint32_t sel) {
+  const uint32_t x = a, y = b;
+  a = med3u(x, y, sel);
+  b = med3u(x, y, ~sel);
+}
+__device__ __forceinline__ void cx_up(uint32_t &a, uint32_t &b) {
+  const uint32_t x = a, y = b;
+  a = x < y ? x : y;
+  b = x < y ? y : x;
+}
+
+template <int LO, int N, int R>
+__device__ __forceinline__ void oem_merge_dir(uint32_t (&key)[32], uint32_t sel) {
+  constexpr int M = 2 * R;
+  if constexpr (M < N) {
+    oem_merge_dir<LO, N, M>(key, sel);
+    oem_merge_dir<LO + R, N, M>(key, sel);
+#pragma unroll
+    for (int i = LO + R; i < LO + N - R; i += M) cx_dir(key[i], key[i + R], sel);
+  } else {
+    cx_dir(key[LO], key[LO + R], sel);
+  }
+}
+template <int LO, int N>
+__device__ __forceinline__ void oem_sort_dir(uint32_t (&key)[32], uint32_t sel) {
+  if constexpr (N > 1) {
+    oem_sort_dir<LO, N / 2>(key, sel);
+    oem_sort_dir<LO + N / 2, N / 2>(key, sel);
+    oem_merge_dir<LO, N, 1>(key, sel);
+  }
+}
+
+__device__ __forceinline__ void lds_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// exchange with lane l ^ LM; bit: this lane's bit of LM, dir: downwards
+template <int LM>
+__device__ __forceinline__ void cx_lanes(uint32_t (&key)[32], bool bit, bool dir) {
+  const uint32_t sel = bit != dir ? 0xffffffffu : 0u;
+#pragma unroll
+  for (int r = 0; r < 32; r++) key[r] = med3u(key[r], (uint32_t)xor_lane<LM>((int)key[r]), sel);
+}
+
+// the merge of 2^M keys (6 <= M <= log2 T), layout A before and after
+template <int T, int M>
+__device__ __forceinline__ void merge_wide(uint32_t (&key)[32], int l, uint32_t *buf) {
+  constexpr int LG = T / 32;
+  constexpr bool LAST = (1 << M) == T;
+  const bool dir = !LAST && ((l >> (M - 5)) & 1);
+  if constexpr (M == 6) {
+    cx_lanes<1>(key, l & 1, dir);
+  } else if constexpr (M == 7) {
+    cx_lanes<2>(key, l & 2, dir);
+    cx_lanes<1>(key, l & 1, dir);
+  } else {
+    // layout B: register hi * P + p holds index 32 hi + LG p + l
+    constexpr int P = 32 / LG;
+#pragma unroll
+    for (int q = 0; q < 8; q++)
+      *(u32x4 *)(buf + l * GROW + 4 * q) = u32x4{key[4 * q], key[4 * q + 1], key[4 * q + 2], key[4 * q + 3]};
+    lds_wave_sync();
+#pragma unroll
+    for (int r = 0; r < 32; r++) key[r] = buf[(r / P) * GROW + (r % P) * LG + l];
+#pragma unroll
+    for (int b = M - 1; b >= 5; b--) {
+      const int j = P << (b - 5), d = LAST ? 0 : P << (M - 5);
+#pragma unroll
+      for (int r = 0; r < 32; r++)
+        if (!(r & j)) {
+          if (r & d) cx_up(key[r | j], key[r]);
+          else cx_up(key[r], key[r | j]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 32; r++) buf[(r / P) * GROW + (r % P) * LG + l] = key[r];
+    lds_wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const u32x4 v = *(const u32x4 *)(buf + l * GROW + 4 * q);
+      key[4 * q] = v.x; key[4 * q + 1] = v.y; key[4 * q + 2] = v.z; key[4 * q + 3] = v.w;
+    }
+    lds_wave_sync();
+  }
+  const uint32_t sel = dir ? 0xffffffffu : 0u;
+#pragma unroll
+  for (int j = 16; j >= 1; j /= 2)
+#pragma unroll
+    for (int r = 0; r < 32; r++)
+      if (!(r & j)) {
+        if constexpr (LAST) cx_up(key[r], key[r | j]);
+        else cx_dir(key[r], key[r | j], sel);
+      }
+  if constexpr (!LAST) merge_wide<T, M + 1>(key, l, buf);
+}
+
+template <int T>
+__global__ __launch_bounds__(256, 4) void k_group_sort(const uint32_t *keys, uint32_t *out, int64_t n) {
+  constexpr int LG = T / 32, GPW = 64 / LG, GS = GroupLds<T>::GS;
+  __shared__ __align__(16) uint32_t s_buf[4][GPW * GS];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l = lane % LG;
+  uint32_t *buf = s_buf[wv] + (lane / LG) * GS;
+  for (int64_t w0 = ((int64_t)blockIdx.x * 4 + wv) * 2048; w0 < n; w0 += (int64_t)gridDim.x * 8192) {
+    const int64_t g0 = w0 + (lane / LG) * T + l * 4;  // the lane's vectors: g0 + 4 LG q
+    const bool full = w0 + 2048 <= n;
+    const int rem = g0 < n ? (n - g0 < 2048 ? (int)(n - g0) : 2048) : 0;  // keys from g0 on
+    uint32_t key[32];
+    if (full) {
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        const u32x4 v = ld_stream4(keys + g0 + 4 * LG * q);
+        key[4 * q] = v.x; key[4 * q + 1] = v.y; key[4 * q + 2] = v.z; key[4 * q + 3] = v.w;
+      }
+    } else {
+      // past n the maximum key; every load is valid and none waits for
+      // another
+      const uint32_t *src = g0 < n ? keys + g0 : keys;
+#pragma unroll
+      for (int r = 0; r < 32; r++) {
+        const int o = 4 * LG * (r / 4) + r % 4;
+        key[r] = src[o < rem ? o : rem > 0 ? rem - 1 : 0];
+      }
+#pragma unroll
+      for (int r = 0; r < 32; r++)
+        if (4 * LG * (r / 4) + r % 4 >= rem) key[r] = 0xffffffffu;
+    }
+    oem_sort_dir<0, 32>(key, l & 1 ? 0xffffffffu : 0u);
+    merge_wide<T, 6>(key, l, buf);
+    // through shared memory to vectors that are consecutive over the wave
+#pragma unroll
+    for (int q = 0; q < 8; q++)
+      *(u32x4 *)(buf + l * GROW + 4 * q) = u32x4{key[4 * q], key[4 * q + 1], key[4 * q + 2], key[4 * q + 3]};
+    lds_wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int v = q * 64 + lane;  // vector of the wave's 2048 keys
+      const u32x4 k4 = *(const u32x4 *)(s_buf[wv] + (v / (T / 4)) * GS + (v % (T / 4)) / 8 * GROW + v % 8 * 4);
+      uint32_t *dst = out + w0 + 4 * v;
+      if (full) {
+        st_stream4(dst, k4.x, k4.y, k4.z, k4.w);
+      } else {
+        const int o = 4 * v, rw = (int)(n - w0);
+        if (o < rw) dst[0] = k4.x;
+        if (o + 1 < rw) dst[1] = k4.y;
+        if (o + 2 < rw) dst[2] = k4.z;
+        if (o + 3 < rw) dst[3] = k4.w;
+      }
+    }
+    lds_wave_sync();  // buf is written again by the next round
   }
 }
 
@@ -377,10 +572,10 @@ static sort_fn pick_sort(int k, int tile) {
   } else if (k == 4) {
     switch (tile) {
     case 64: return k_tile_sort<4, 64>;
-    case 128: return k_tile_sort<4, 128>;
-    case 256: return k_tile_sort<4, 256>;
-    case 512: return k_tile_sort<4, 512>;
-    case 1024: return k_tile_sort<4, 1024>;
+    case 128: return k_group_sort<128>;
+    case 256: return k_group_sort<256>;
+    case 512: return k_group_sort<512>;
+    case 1024: return k_group_sort<1024>;
     }
   }
   return nullptr;
@@ -413,14 +608,27 @@ extern "C" cox_status cox_tile_sort(const uint32_t *keys, uint32_t *out, int64_t
   if (!aligned16(keys) || !aligned16(out)) return COX_ERR_ALIGN;
   const int64_t nvec = (n + k - 1) / k;
   const int U = k >= 16 ? 1 : 16 / k > 4 ? 4 : 16 / k;
+  const int32_t want = cfg ? cfg->grid_blocks : 0;
+  if (k == 4 && tile >= 128) {
+    // k_group_sort: a block per 8192 keys, all of them launched (2^26 keys
+    // in 1024-key groups: 128 us, 137 with a grid that fills the device)
+    const int64_t items = (n + 8191) / 8192, most = want ? want : 0x7fffffff;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, (hipStream_t)stream, keys, out,
+                       n);
+    return launch_status();
+  }
   // default blocks per compute unit (measured at 2^28 keys): two for
   // 32-key groups and for 64-key groups with several keys per lane; six
   // for 64 keys over a full wave (0.420 ms against 0.434 with eight); eight
-  // for wider groups, whose longer networks need more waves in flight
-  // (1024-key groups: 0.69 ms against 0.95 ms with two)
-  const int per_cu = tile == 32 || (k >= 2 && tile <= 64) ? 2 : tile == 64 ? 6 : 8;
-  const int grid = persistent_grid((const void *)fn, 256, (nvec + 256 * U - 1) / (256 * U),
-                                   cfg ? cfg->grid_blocks : 0, 0, per_cu);
+  // for the other one-key forms, whose longer networks need more waves in
+  // flight.  Where two would take more than one round and six do not, all
+  // rounds are launched at once: 2^22 + 17 keys in 32-key groups 7.5 us
+  // against 9.8, in 64-key groups 8.2 against 11.4 (past that, two: 2^23
+  // keys 14.9 us against 15.3 with six, 2^28 355 against 380).
+  const int64_t items = (nvec + 256 * U - 1) / (256 * U);
+  const int two = items <= 6 * (int64_t)device_cus() ? 6 : 2;
+  const int per_cu = tile == 32 || (k >= 2 && tile <= 64) ? two : tile == 64 ? 6 : 8;
+  const int grid = persistent_grid((const void *)fn, 256, items, want, 0, per_cu);
   hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, (hipStream_t)stream, keys, out, n);
   return launch_status();
 }
