@@ -10,7 +10,8 @@
 // every chunk partial is published as a 64-bit word [tag | value bits]
 // with a device-scope atomic store (tag = this call's epoch), and the last
 // block to finish (device-scope counter) collects the words, checking each
-// tag, and runs the FP64 (or int64) final combine.  No memory fences are
+// tag, and runs the FP64 (or int64) final combine.  A single chunk's value is
+// the total at once.  No memory fences are
 // needed: a word with the current tag can only hold this call's partial,
 // and the last block resets the counter and advances the epoch only after
 // it has seen every block's words, whose tags every block derived from its
@@ -65,12 +66,10 @@ template <> struct ElemT<DT_I32> { static constexpr int size = 4; };
 template <> struct ElemT<DT_F32> { static constexpr int size = 4; };
 template <> struct ElemT<DT_BF16> { static constexpr int size = 2; };
 
-// raw 32-bit value of element v of a vector of V elements (bfloat16 widened)
-template <int ESZ, int V>
-__device__ __forceinline__ void load_vec(const void *__restrict__ base, int64_t idx, uint32_t (&r)[V]) {
-  constexpr int BYTES = ESZ * V;
-  const char *p = (const char *)base + idx * ESZ;
-  uint32_t w[(BYTES + 3) / 4];
+// a vector of V elements as it lies in memory: NW words (a 2-byte vector in
+// the low half of its word)
+template <int BYTES>
+__device__ __forceinline__ void load_raw(const char *p, uint32_t (&w)[(BYTES + 3) / 4]) {
   if constexpr (BYTES == 16) {
     const u32x4 q = ld_stream4(p);
     w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
@@ -82,19 +81,13 @@ __device__ __forceinline__ void load_vec(const void *__restrict__ base, int64_t 
   } else {
     w[0] = ld_stream_h(p);
   }
-  if constexpr (ESZ == 4) {
-#pragma unroll
-    for (int v = 0; v < V; v++) r[v] = w[v];
-  } else {
-#pragma unroll
-    for (int v = 0; v < V; v++) r[v] = (v & 1) ? (w[v >> 1] & 0xffff0000u) : (w[v >> 1] << 16);
-  }
 }
 
-template <int ESZ>
-__device__ __forceinline__ uint32_t load_one(const void *__restrict__ base, int64_t idx) {
-  if constexpr (ESZ == 4) return ld_stream1((const uint32_t *)base + idx);
-  else return (uint32_t)ld_stream_h((const uint16_t *)base + idx) << 16;
+// raw 32-bit value of element v of such a vector (bfloat16 widened)
+template <int ESZ, int NW>
+__device__ __forceinline__ uint32_t element(const uint32_t (&w)[NW], int v) {
+  if constexpr (ESZ == 4) return w[v];
+  else return (v & 1) ? (w[v >> 1] & 0xffff0000u) : (w[v >> 1] << 16);
 }
 
 // per-lane accumulator
@@ -252,6 +245,30 @@ __device__ __forceinline__ void take_words(const uint64_t *p, int64_t i0, int64_
   }
 }
 
+// Counts this block as done; true for the last one of the grid.  Atomics on
+// one 64-byte unit take 11.5 ns each, one after another, and all blocks of a
+// full grid arrive at about the same time (256: 3 us), so larger grids count
+// in four groups, each on a unit of its own in the header, and then the
+// groups.  (One round trip more, 0.45 us, so small grids count directly.)
+__device__ __forceinline__ bool count_done(uint32_t *hdr) {
+  const uint32_t G = gridDim.x;
+  if (G <= 64) return add_dev32(&hdr[HDR_DONE], 1u) == G - 1;
+  const uint32_t g = blockIdx.x & 3u, members = (G - g + 3u) >> 2;
+  uint32_t *const word = &hdr[g ? 16u * g : (uint32_t)HDR_GROUP0];
+  if (add_dev32(word, 1u) != members - 1) return false;
+  st_dev32(word, 0u);
+  return add_dev32(&hdr[HDR_DONE], 1u) == 3u;
+}
+
+// Full chunks c = blockIdx.x + i * gridDim.x run double-buffered: the next
+// chunk's vectors are requested before the current chunk is reduced, so loads
+// stay in flight across the block's barrier.  A buffer holds the vectors as
+// they lie in memory and elements are widened where they are used: widened at
+// the load, bfloat16 vectors took twice the registers, and the compiler
+// waited for one chunk before it requested the next (dot of 2^28 bfloat16,
+// TwoSum: 179 -> 165 us; of 2^28 float32: 373 -> 341; sum: 179 -> 162).  Past the block's last full chunk
+// the request is kept (loads stay unconditional) but every lane reads the
+// array's first vector: one line, not a chunk.
 template <int K, int DT, int OP, int ACC>
 __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, const void *__restrict__ y,
                                                  int64_t n, int64_t nch, void *__restrict__ part,
@@ -259,95 +276,162 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   constexpr int ESZ = ElemT<DT>::size;
   constexpr int V = K < 16 / ESZ ? K : 16 / ESZ;
   constexpr int R = K / V;
-  constexpr uint32_t XPAD = DT == DT_I32 ? 0u : 0x80000000u;  // -0.0f
-  constexpr uint32_t YPAD = 0u;                                // +0.0f
-  __shared__ Acc slot[32];
+  constexpr int VB = V * ESZ, NW = (VB + 3) / 4;
+  constexpr int NA = OP == OP_DOT ? 2 : 1;
+  // padding of x (-0.0, or 0 for int32) and y (+0.0), as raw words
+  constexpr uint32_t XPAD = DT == DT_I32 ? 0u : DT == DT_BF16 ? 0x80008000u : 0x80000000u;
+  __shared__ Acc slot[2][32];
   __shared__ double fin[256];
   __shared__ uint32_t s_last, s_epoch;
 
   const int W = blockDim.x >> 5;
   uint64_t *pw = (uint64_t *)(hdr + HDR_WORDS);
-  if (threadIdx.x == 0) s_epoch = ld_dev32(&hdr[HDR_EPOCH]);
-  __syncthreads();
-  const uint32_t epoch = s_epoch;
-  const uint32_t tag = tag_of_epoch(epoch);
+  // thread 0 stores the partials, so it alone needs the epoch until the
+  // final combine; its load is not waited for before the data's
+  uint32_t epoch = 0u;
+  if (threadIdx.x == 0) epoch = ld_dev32(&hdr[HDR_EPOCH]);
   const int w = threadIdx.x >> 5, l = threadIdx.x & 31;
   const int64_t S = (int64_t)blockDim.x * K;
+  const bool single = nch == 1 && gridDim.x == 1;  // its value is the total
+  int par = 0;
 
-  // Full chunks c = blockIdx.x + i * gridDim.x run double-buffered: the
-  // next chunk's vectors are requested before the current chunk is
-  // reduced, so loads stay in flight across the block's barriers.  Past the
-  // block's last full chunk the request is kept (loads stay unconditional)
-  // but every lane reads the array's first vector: one line, not a chunk.
-  // The partial last chunk (if any) is reduced afterwards with element-wise
-  // bounds.
   const int64_t nfull = n / S;
-  auto load_full = [&](int64_t c, uint32_t (&xr)[R][V], uint32_t (&yr)[R][V]) {
+  typedef uint32_t Buf[NA][R][NW];
+  auto load_full = [&](int64_t c, Buf &r) {
     const bool dummy = c >= nfull;
-    // one base index and one row stride per lane (not a select per load)
-    const int64_t b0 = dummy ? 0 : c * S + (int64_t)w * 32 * K + (int64_t)l * V;
-    const int rs = dummy ? 0 : 32 * V;
+    // one base offset and one row stride per lane (not a select per load)
+    const int64_t b0 = (dummy ? 0 : c * S + (int64_t)w * 32 * K + (int64_t)l * V) * ESZ;
+    const int rs = dummy ? 0 : 32 * VB;
 #pragma unroll
     for (int i = 0; i < R; i++) {
-      load_vec<ESZ, V>(x, b0 + (int64_t)i * rs, xr[i]);
-      if constexpr (OP == OP_DOT) load_vec<ESZ, V>(y, b0 + (int64_t)i * rs, yr[i]);
+      load_raw<VB>((const char *)x + b0 + i * rs, r[0][i]);
+      if constexpr (NA == 2) load_raw<VB>((const char *)y + b0 + i * rs, r[NA - 1][i]);
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto reduce_chunk = [&](int64_t c, const uint32_t (&xr)[R][V], const uint32_t (&yr)[R][V]) {
+  auto reduce_chunk = [&](int64_t c, const Buf &r) {
     Acc a = acc_identity<DT, ACC>();
 #pragma unroll
     for (int i = 0; i < R; i++)
 #pragma unroll
-      for (int v = 0; v < V; v++) acc_step<DT, OP, ACC>(a, xr[i][v], OP == OP_DOT ? yr[i][v] : 0u);
+      for (int v = 0; v < V; v++)
+        acc_step<DT, OP, ACC>(a, element<ESZ>(r[0][i], v), NA == 2 ? element<ESZ>(r[NA - 1][i], v) : 0u);
     a = warp_tree<DT, ACC>(a);
-    if (l == 0) slot[w] = a;
+    // two sets of slots: warp 0 reads this chunk's before it comes to the
+    // next chunk's barrier, past which they are written again
+    if (l == 0) slot[par][w] = a;
     __syncthreads();
     if (w == 0) {
-      Acc b = l < W ? slot[l] : acc_identity<DT, ACC>();
+      Acc b = l < W ? slot[par][l] : acc_identity<DT, ACC>();
       b = warp_tree<DT, ACC>(b);
-      if (l == 0) store_partial<DT, ACC>(part, pw, tag, c, b);
+      if (l == 0) {
+        if (single) {
+          // one chunk: the final combine of its value alone
+          if constexpr (DT == DT_I32) {
+            if (part) ((int32_t *)part)[0] = (int32_t)b.i;
+            *(long long *)total = (long long)(int32_t)b.i;
+          } else if constexpr (ACC == COX_ACC_PLAIN) {
+            if (part) ((float *)part)[0] = b.s;
+            *(double *)total = -0.0 + (double)b.s;
+          } else {
+            if (part) ((float2 *)part)[0] = make_float2(b.s, b.c);
+            *(double *)total = -0.0 + ((double)b.s + (double)b.c);
+          }
+        } else {
+          store_partial<DT, ACC>(part, pw, tag_of_epoch(epoch), c, b);
+        }
+      }
     }
-    __syncthreads();
+    par ^= 1;
   };
   if (nfull > 0) {
-    uint32_t xa[R][V], ya[R][V], xb[R][V], yb[R][V];
+    Buf A, B;
     int64_t c = blockIdx.x;
-    load_full(c, xa, ya);
+    load_full(c, A);
     while (c < nfull) {
       int64_t cn = c + gridDim.x;
-      load_full(cn, xb, yb);
-      reduce_chunk(c, xa, ya);
+      load_full(cn, B);
+      reduce_chunk(c, A);
       c = cn;
       if (c >= nfull) break;
       cn = c + gridDim.x;
-      load_full(cn, xa, ya);
-      reduce_chunk(c, xb, yb);
+      load_full(cn, A);
+      reduce_chunk(c, B);
       c = cn;
     }
   }
   if (nfull * S < n && blockIdx.x == nfull % gridDim.x) {
-    uint32_t xr[R][V], yr[R][V];
-    const int64_t wbase = nfull * S + (int64_t)w * 32 * K;
+    // the partial last chunk, every load unconditional so that all are in
+    // flight together: vectors past n read vector 0 and become padding, and
+    // every lane reads the elements of the vector that n cuts (at edge)
+    const int64_t e0 = nfull * S + (int64_t)w * 32 * K + (int64_t)l * V;
+    const int64_t edge = n / V * V;
+    Buf r;
+    uint32_t cut[NA][NW];
 #pragma unroll
-    for (int i = 0; i < R; i++)
+    for (int k = 0; k < NW; k++) {
+      cut[0][k] = XPAD;
+      if constexpr (NA == 2) cut[NA - 1][k] = 0u;
+    }
+    if (edge < n) {
+      uint32_t h[NA][V];
 #pragma unroll
       for (int v = 0; v < V; v++) {
-        const int64_t e = wbase + (int64_t)(i * 32 + l) * V + v;
-        xr[i][v] = e < n ? load_one<ESZ>(x, e) : XPAD;
-        yr[i][v] = (OP == OP_DOT && e < n) ? load_one<ESZ>(y, e) : YPAD;
+        const int64_t e = edge + v < n ? edge + v : n - 1;
+        if constexpr (ESZ == 4) h[0][v] = ((const uint32_t *)x)[e];
+        else h[0][v] = ((const uint16_t *)x)[e];
+        if constexpr (NA == 2) {
+          if constexpr (ESZ == 4) h[NA - 1][v] = ((const uint32_t *)y)[e];
+          else h[NA - 1][v] = ((const uint16_t *)y)[e];
+        }
       }
-    reduce_chunk(nfull, xr, yr);
+#pragma unroll
+      for (int v = 0; v < V; v++)
+#pragma unroll
+        for (int k = 0; k < NA; k++) {
+          uint32_t &word = cut[k][v * ESZ / 4];
+          const int sh = ESZ == 4 ? 0 : 16 * (v & 1);
+          const uint32_t m = (ESZ == 4 ? 0xffffffffu : 0xffffu) << sh;
+          if (edge + v < n) word = (word & ~m) | (h[k][v] << sh);
+        }
+    }
+    if (edge > 0) {
+#pragma unroll
+      for (int i = 0; i < R; i++) {
+        const int64_t e = e0 + i * 32 * V, b0 = (e < edge ? e : 0) * ESZ;
+        load_raw<VB>((const char *)x + b0, r[0][i]);
+        if constexpr (NA == 2) load_raw<VB>((const char *)y + b0, r[NA - 1][i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const int64_t e = e0 + i * 32 * V;
+      if (e >= edge) {
+#pragma unroll
+        for (int k = 0; k < NW; k++) {
+          r[0][i][k] = e == edge ? cut[0][k] : XPAD;
+          if constexpr (NA == 2) r[NA - 1][i][k] = e == edge ? cut[NA - 1][k] : 0u;
+        }
+      }
+    }
+    reduce_chunk(nfull, r);
   }
+  if (single) return;
 
   // the last block to finish combines the chunk partials
-  if (threadIdx.x == 0) s_last = (add_dev32(&hdr[HDR_DONE], 1u) == gridDim.x - 1) ? 1u : 0u;
+  if (threadIdx.x == 0) {
+    s_epoch = epoch;
+    s_last = count_done(hdr) ? 1u : 0u;
+  }
   __syncthreads();
   if (!s_last) return;
+  epoch = s_epoch;
+  const uint32_t tag = tag_of_epoch(epoch);
 
   // Loads of the partials are issued in batches of FB independent loads per
   // thread before they are added, so the fixed serial order costs one
   // memory latency per batch rather than one per chunk.
-  constexpr int FB = 32;
+  constexpr int FB = ACC == COX_ACC_PLAIN ? 32 : 8;  // TwoSum: two words a chunk, and no spills
   if constexpr (DT == DT_I32) {
     __shared__ long long isum[32];
     long long s = 0;
@@ -361,12 +445,14 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
     for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
     if (l == 0) isum[w] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      long long tot = 0;
-      for (int j = 0; j < W; j++) tot += isum[j];
-      *(long long *)total = tot;
-      st_dev32(&hdr[HDR_DONE], 0u);
-      st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
+    if (threadIdx.x < 32) {
+      long long tot = l < W ? isum[l] : 0;
+      for (int o = 16; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 32);
+      if (l == 0) {
+        *(long long *)total = tot;
+        st_dev32(&hdr[HDR_DONE], 0u);
+        st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
+      }
     }
   } else {
     // FP64 final tree shaped like a 256-thread block (see cox.h); a chain
@@ -391,16 +477,26 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
 #pragma unroll
         for (int b = 0; b < FB; b++) s = s + buf[b];
       }
-      fin[j] = s;
+      // the tree of each group of 32, by its own warp where there are eight
+      if (blockDim.x >= 256) {
+        s = tree_f64(s);
+        if (l == 0) fin[j >> 5] = s;
+      } else {
+        fin[j] = s;
+      }
     }
     __syncthreads();
     if (threadIdx.x < 32) {
       double top = -0.0;
+      if (blockDim.x >= 256) {
+        if (l < 8) top = fin[l];
+      } else {
 #pragma unroll 1
-      for (int vw = 0; vw < 8; vw++) {
-        const double r = tree_f64(fin[32 * vw + l]);
-        const double r0 = __shfl(r, 0, 32);
-        if (l == vw) top = r0;
+        for (int vw = 0; vw < 8; vw++) {
+          const double r = tree_f64(fin[32 * vw + l]);
+          const double r0 = __shfl(r, 0, 32);
+          if (l == vw) top = r0;
+        }
       }
       top = tree_f64(top);
       if (l == 0) {
