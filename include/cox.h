@@ -440,12 +440,12 @@ cox_status cox_plan_destroy(cox_plan plan);
  * img: device uint8[height][width], row-major; sat: device
  * uint32[height][width].  Tiles of 64 rows x 1024 columns are reduced
  * (column sums, row sums, tile totals), the column sums are scanned down
- * the bands, and every tile is then scanned row by row (a 32-lane shuffle
- * scan per row) with its carries from above and from the left: three
+ * the bands, and every tile is then scanned row by row (a shuffle scan of
+ * 256 columns per wave and row) with its carries from above and from the left: three
  * launches, about 6.1 bytes per pixel.  The result is exact (uint32
- * arithmetic).  A width that is a multiple of 4 with img 4-byte and sat
- * 16-byte aligned uses 4-pixel loads and 16-byte stores; any other shape
- * works element by element.  ws: cox_workspace_bytes(COX_OP_INTEGRAL_IMAGE,
+ * arithmetic).  Any shape and alignment (sat 4-byte) uses vector loads and
+ * stores; aligned ones for widths that are multiples of 16 (tile sums) and 4
+ * (tile scans).  ws: cox_workspace_bytes(COX_OP_INTEGRAL_IMAGE,
  * COX_U32, height, width, NULL). */
 cox_status cox_integral_image(const uint8_t *img, int64_t height, int64_t width, uint32_t *sat, void *ws,
                               size_t ws_bytes, void *stream);

@@ -6,9 +6,9 @@
 // per pixel: 1 + 4 read, 4 + 4 written), the image is cut into tiles of
 // TH rows x TW columns (band b, segment s) and reduced, carried, then
 // scanned:
-//   k_ii_reduce  per tile (k_ii_reduce16 with 16-pixel loads where the
-//                shape allows): column sums (colsum[b][x]), row sums
-//                (rowsum[s][y]) and the tile total (total[b][s]);
+//   k_ii_reduce16 (k_ii_reduce below 16 columns) per tile: column sums
+//                (colsum[b][x]), row sums (rowsum[s][y]) and the tile total
+//                (total[b][s]);
 //   k_ii_colscan per column: colsum[b][x] replaced by its exclusive prefix
 //                over the bands above, T[b][x] (8 waves per 64 columns);
 //   k_ii_scan    per tile: sat[y][x] = rowprefix_x(T[b][.] + column sums
@@ -16,8 +16,8 @@
 //                with L[y] the row sums of the segments to the left and
 //                corner the totals of the tiles above and to the left.
 // Every row of a tile is an inclusive scan over TW columns: lane-serial
-// over a thread's 4 columns, a 32-lane shuffle scan (DPP row shifts), and
-// the warp totals combined in shared memory.  About 6.1 bytes per pixel
+// over a lane's 4 columns, a shuffle scan over the wave (DPP row shifts), and
+// the waves' sums through shared memory.  About 6.1 bytes per pixel
 // move (the image is read twice), all in uint32 arithmetic, so the result
 // is exact (mod 2^32) whatever the order.
 #include "cox_internal.hpp"
@@ -28,10 +28,8 @@ constexpr int II_TH = 64;     // rows per tile
 constexpr int II_TW = 1024;   // columns per tile
 constexpr int II_BT = 256;    // threads per block, 4 columns each
 constexpr int II_RB = 8;      // rows per round of the reduce kernel (its butterfly sums 8)
-constexpr int II_RS = 4;      // rows per shared-memory round of the scan kernel (measured: 4 rows
-                              // 93 us, 8 rows 99 us, 16 rows 106 us at 8192 x 8192)
-// wave 0 (64 threads) handles the tile's rows: one row per thread, two
-// logical warps
+// wave 0 (64 threads) of the reduce kernel handles the tile's rows: one row
+// per thread, two logical warps
 static_assert(II_TH == 64 && II_BT >= 64 && II_TW == 4 * II_BT, "tile shape the kernels assume");
 
 // inclusive scan over the 32 lanes of a logical warp
@@ -63,20 +61,49 @@ struct IiArgs {
   uint32_t *total;    // [nb][ns]
 };
 
-// The 4 pixels of a thread in row y (columns x .. x + 3; zero past W, and
-// zero for rows past the tile).  VEC (W % 4 == 0, image 4-byte aligned):
-// one 4-byte load.
-template <bool VEC>
-__device__ __forceinline__ void ii_pixels(const IiArgs &a, int64_t y, bool row_ok, int64_t x, uint32_t (&p)[4]) {
-  const uint8_t *row = a.img + y * a.W;
-  if constexpr (VEC) {
-    const uint32_t w = row_ok && x < a.W ? ld_stream1(row + x) : 0u;
-#pragma unroll
-    for (int j = 0; j < 4; j++) p[j] = (w >> (8 * j)) & 0xffu;
+// Tile number of work item i: the tiles are handed out so that each XCD
+// (blocks b mod 8) walks an eighth of the image that is contiguous in memory.
+// In plain order an XCD got the same 1024 columns of every band whenever a row
+// has 8 segments, so its traffic met one eighth of the memory channels:
+// 8192 x 8192 pixels 89.7 us, 76.4 in this order (8192 x 8000: 80.2 and 79.1,
+// 6016 x 6016: 49.4 and 48.9).
+__device__ __forceinline__ int64_t ii_tile(int64_t i, int64_t tiles) {
+  const int64_t per = tiles >> 3;
+  return i < 8 * per ? (i & 7) * per + (i >> 3) : i;
+}
+
+// How pixels are loaded: VEC (W % 4 == 0, image 4-byte aligned): aligned
+// words; ANY: words at any address, the last lane of a row reading the row's
+// last four bytes; NARROW (W < 4): bytes
+enum { II_VEC = 0, II_ANY = 1, II_NARROW = 2 };
+typedef uint32_t ii_u32u __attribute__((aligned(1)));
+typedef uint32_t ii_u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// the cols (1 .. 4) pixels of a lane at p, column j in byte j, zero above
+template <int MODE>
+__device__ __forceinline__ uint32_t ii_word(const uint8_t *p, int cols) {
+  if constexpr (MODE == II_VEC) {
+    return ld_stream1(p);
+  } else if constexpr (MODE == II_ANY) {
+    return *(const ii_u32u *)(p - (4 - cols)) >> (8 * (4 - cols));
   } else {
-#pragma unroll
-    for (int j = 0; j < 4; j++) p[j] = row_ok && x + j < a.W ? (uint32_t)row[x + j] : 0u;
+    return (uint32_t)p[0] | (cols > 1 ? (uint32_t)p[1] << 8 : 0u) | (cols > 2 ? (uint32_t)p[2] << 16 : 0u);
   }
+}
+
+// the lane's columns x .. x + 3 that lie in the image
+__device__ __forceinline__ int ii_cols(const IiArgs &a, int64_t x) {
+  return x < a.W ? (a.W - x < 4 ? (int)(a.W - x) : 4) : 0;
+}
+
+// The 4 pixels of a thread in row y (columns x .. x + 3; zero past W, and
+// zero for rows past the tile).
+template <int MODE>
+__device__ __forceinline__ void ii_pixels(const IiArgs &a, int64_t y, bool row_ok, int64_t x, int cols,
+                                          uint32_t (&p)[4]) {
+  const uint32_t w = row_ok && cols ? ii_word<MODE>(a.img + y * a.W + x, cols) : 0u;
+#pragma unroll
+  for (int j = 0; j < 4; j++) p[j] = (w >> (8 * j)) & 0xffu;
 }
 
 // Sums of 8 values over a logical warp, one value per row: a butterfly
@@ -103,21 +130,21 @@ __device__ __forceinline__ uint32_t ii_warp_sum8(const uint32_t (&v)[8]) {
   return c;
 }
 
-template <bool VEC>
+template <int MODE>
 __global__ __launch_bounds__(II_BT) void k_ii_reduce(IiArgs a) {
   static_assert(II_RB == 8, "row sums are reduced 8 rows at a time");
   __shared__ uint32_t s_rows[II_BT / 32][II_TH];
   __shared__ uint32_t s_tot[2];
   const int t = threadIdx.x, w = t >> 5, l = t & 31;
-  for (int64_t tile = blockIdx.x; tile < a.nb * a.ns; tile += gridDim.x) {
-    const int64_t b = tile / a.ns, s = tile % a.ns;
+  for (int64_t i = blockIdx.x; i < a.nb * a.ns; i += gridDim.x) {
+    const int64_t tile = ii_tile(i, a.nb * a.ns), b = tile / a.ns, s = tile % a.ns;
     const int64_t y0 = b * II_TH, x = s * II_TW + 4 * t;
-    const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH);
+    const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH), cols = ii_cols(a, x);
     uint32_t cs[4] = {0u, 0u, 0u, 0u};
     for (int r0 = 0; r0 < rows; r0 += II_RB) {
       uint32_t p[II_RB][4];
 #pragma unroll
-      for (int r = 0; r < II_RB; r++) ii_pixels<VEC>(a, y0 + r0 + r, r0 + r < rows, x, p[r]);
+      for (int r = 0; r < II_RB; r++) ii_pixels<MODE>(a, y0 + r0 + r, r0 + r < rows, x, cols, p[r]);
       uint32_t rp[II_RB];
 #pragma unroll
       for (int r = 0; r < II_RB; r++) {
@@ -177,20 +204,38 @@ __device__ __forceinline__ uint32_t ii_wave_sum16(const uint32_t (&v)[16]) {
   return d;
 }
 
-// Tile sums with 16-pixel loads (width a multiple of 16, image 16-byte
-// aligned).  Lane c of wave g covers columns 16c .. 16c + 15 of the tile
-// and rows g, g + 4, .., g + 60, so a row's sum is a wave sum; the four
-// waves' column sums meet in shared memory.  Same outputs as k_ii_reduce.
-__global__ __launch_bounds__(II_BT) void k_ii_reduce16(IiArgs a) {
+// the 128-bit value w shifted down by sh (0 .. 127) bits
+__device__ __forceinline__ u32x4 ii_shift_down(u32x4 w, int sh) {
+  uint64_t lo = w.x | (uint64_t)w.y << 32, hi = w.z | (uint64_t)w.w << 32;
+  if (sh >= 64) {
+    lo = hi;
+    hi = 0u;
+  }
+  sh &= 63;
+  lo = lo >> sh | (hi << 1) << (63 - sh);
+  hi >>= sh;
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+typedef uint32_t ii_u32x4b __attribute__((ext_vector_type(4), aligned(1)));
+
+// Tile sums with 16-pixel loads (width at least 16).  Lane c of wave g covers
+// columns 16c .. 16c + 15 of the tile and rows g, g + 4, .., g + 60, so a
+// row's sum is a wave sum; the four waves' column sums meet in shared memory.
+// VEC: width a multiple of 16, image 16-byte aligned.  ANY: vectors at any
+// address, a row's last, partial lane reading its last 16 bytes (1999 x 3001
+// pixels: 21.5 us with 4-pixel loads, 6.6).  Same outputs as k_ii_reduce.
+template <int MODE>
+__global__ __launch_bounds__(II_BT, 4) void k_ii_reduce16(IiArgs a) {
   static_assert(II_BT == 256 && II_TW == 1024 && II_TH == 64, "4 waves x 64 lanes x 16 columns, 16 rows a wave");
   __shared__ __align__(16) uint32_t s_col[4][II_TW];
   __shared__ uint32_t s_tot[4];
   const int t = threadIdx.x, g = t >> 6, L = t & 63;
-  for (int64_t tile = blockIdx.x; tile < a.nb * a.ns; tile += gridDim.x) {
-    const int64_t b = tile / a.ns, s = tile % a.ns;
+  for (int64_t i = blockIdx.x; i < a.nb * a.ns; i += gridDim.x) {
+    const int64_t tile = ii_tile(i, a.nb * a.ns), b = tile / a.ns, s = tile % a.ns;
     const int64_t y0 = b * II_TH, x = s * II_TW + 16 * L;
     const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH);
     const bool okx = x < a.W;
+    const int back = MODE == II_ANY && okx && a.W - x < 16 ? 16 - (int)(a.W - x) : 0;  // of a partial lane
     // column sums packed two to a word (even and odd bytes in 16-bit
     // halves; at most 16 * 255 each, no carry between halves), row sums by
     // v_sad_u8 against zero; rows in two batches of 8 loads
@@ -201,8 +246,18 @@ __global__ __launch_bounds__(II_BT) void k_ii_reduce16(IiArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; i++) {
         const int r = g + 4 * (i0 + i);
-        px[i] = okx && r < rows ? ld_stream4(a.img + (y0 + r) * a.W + x) : u32x4{0u, 0u, 0u, 0u};
+        const uint8_t *p = a.img + (y0 + (r < rows ? r : 0)) * a.W + (okx ? x - back : 0);
+        if constexpr (MODE == II_VEC) px[i] = ld_stream4(p);
+        else px[i] = __builtin_nontemporal_load((const ii_u32x4b *)p);
       }
+      if constexpr (MODE == II_ANY)
+        if (s == a.ns - 1) {
+#pragma unroll
+          for (int i = 0; i < 8; i++) px[i] = ii_shift_down(px[i], 8 * back);
+        }
+#pragma unroll
+      for (int i = 0; i < 8; i++)
+        if (!okx || g + 4 * (i0 + i) >= rows) px[i] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
       for (int i = 0; i < 8; i++) {
         uint32_t sum = 0u;
@@ -244,7 +299,16 @@ __global__ __launch_bounds__(II_BT) void k_ii_reduce16(IiArgs a) {
       uint32_t out[4];
 #pragma unroll
       for (int j = 0; j < 4; j++) out[j] = s_col[0][c0 + j] + s_col[1][c0 + j] + s_col[2][c0 + j] + s_col[3][c0 + j];
-      if (xc < a.W) *(u32x4 *)&a.colsum[b * a.W + xc] = u32x4{out[0], out[1], out[2], out[3]};
+      uint32_t *dst = &a.colsum[b * a.W + xc];
+      if constexpr (MODE == II_VEC) {
+        if (xc < a.W) *(u32x4 *)dst = u32x4{out[0], out[1], out[2], out[3]};
+      } else if (xc + 4 <= a.W) {
+        *(ii_u32x4u *)dst = ii_u32x4u{out[0], out[1], out[2], out[3]};
+      } else {
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+          if (xc + j < a.W) dst[j] = out[j];
+      }
     }
     if (t == 0) a.total[b * a.ns + s] = s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3];
     __syncthreads();
@@ -291,90 +355,113 @@ __global__ __launch_bounds__(64 * II_CS_WAVES) void k_ii_colscan(IiArgs a) {
   }
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(II_BT) void k_ii_scan(IiArgs a) {
-  __shared__ uint32_t s_lin[II_TH];             // row carries, prefixed inside each 32-row half
-  __shared__ uint32_t s_left[II_TH];            // corner + row carries, prefixed over the tile's rows
-  __shared__ uint32_t s_wt[2][II_RS][II_BT / 32];  // warp totals of a round of rows
-  __shared__ uint32_t s_red[II_BT / 32];
-  const int t = threadIdx.x, w = t >> 5, l = t & 31;
-  int buf = 0;
-  for (int64_t tile = blockIdx.x; tile < a.nb * a.ns; tile += gridDim.x) {
-    const int64_t b = tile / a.ns, s = tile % a.ns;
+// inclusive scan over the 64 lanes of the wave
+__device__ __forceinline__ uint32_t ii_wave_scan(uint32_t v) {
+  v = ii_warp_scan(v);
+  v += (uint32_t)dpp<0x143, 0xc>(0, (int)v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// One step of the butterfly below: 2H values to H, lanes exchanging with
+// lane ^ M (the lane's bit of M says which half it keeps).
+template <int M, int H>
+__device__ __forceinline__ void ii_halve(uint32_t (&v)[64], int lane) {
+  const bool up = (lane & M) != 0;
+#pragma unroll
+  for (int i = 0; i < H; i++) {
+    const uint32_t keep = up ? v[i + H] : v[i], send = up ? v[i] : v[i + H];
+    if constexpr (M == 32) v[i] = keep + ii_xor32(send);
+    else v[i] = keep + (uint32_t)xor_lane<M>((int)send);
+  }
+}
+
+// Tile scans.  Wave w of the block holds columns 256w .. 256w + 255 of the
+// tile (4 a lane) and all its 64 rows: every pixel is requested before
+// anything else, 64 words a lane, so no row waits for memory.  Of the other
+// waves it needs the sums of their column carries and their row sums, which a
+// butterfly leaves one row per lane, so the block meets at one barrier per
+// tile; the carry of row y (corner, segments and waves to the left, over the
+// rows up to y) is then a scan over the lanes, and row y takes it from lane y.
+// Bound by the table's stores.  Reading four rows at a time, with a barrier
+// and shared-memory warp totals for each four, the rounds' latency bound it:
+// the same 70 us whatever the order of the tiles; now 55 us for 8192 x 8192
+// pixels (see ii_tile), 4.9 TB/s of image and table.
+template <int MODE>
+__global__ __launch_bounds__(II_BT, 4) void k_ii_scan(IiArgs a) {
+  static_assert(II_TH == 64 && II_TW == 4 * 256 && II_BT == 256, "a wave per 256 columns, a lane per row");
+  __shared__ uint32_t s_rt[4][II_TH], s_above[4];  // the waves' row sums, sums of their column carries
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  for (int64_t i = blockIdx.x; i < a.nb * a.ns; i += gridDim.x) {
+    const int64_t tile = ii_tile(i, a.nb * a.ns), b = tile / a.ns, s = tile % a.ns;
     const int64_t y0 = b * II_TH, x = s * II_TW + 4 * t;
-    const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH);
-    // corner: totals of the tiles above and to the left
-    uint32_t cv = 0u;
-    for (int64_t k = t; k < b * s; k += II_BT) cv += a.total[(k / s) * a.ns + (k % s)];
-    cv = ii_warp_sum(cv);
-    if (l == 0) s_red[w] = cv;
-    // row carries (thread t < TH: row y0 + t): row sums of the segments to
-    // the left, then an inclusive scan inside each 32-row half
-    uint32_t lv = 0u;
-    if (t < rows && t < II_TH)
-      for (int64_t k = 0; k < s; k++) lv += a.rowsum[k * a.H + y0 + t];
-    lv = ii_warp_scan(lv);
-    if (t < II_TH) s_lin[t] = lv;
+    const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH), cols = ii_cols(a, x);
+    // pixels of row r (column x + j in byte j); rows and lanes past the image
+    // read a valid row or the row's start and are cleared below
+    uint32_t px[II_TH];
+    const uint8_t *src = a.img + y0 * a.W + (cols ? x : 0);
+    const int load_cols = cols ? cols : (a.W < 4 ? (int)a.W : 4);
+#pragma unroll
+    for (int r = 0; r < II_TH; r++) px[r] = ii_word<MODE>(src + (r < rows ? r : rows - 1) * a.W, load_cols);
     // column carries: the band sums above
     uint32_t c[4];
 #pragma unroll
-    for (int j = 0; j < 4; j++) c[j] = x + j < a.W ? a.colsum[b * a.W + x + j] : 0u;
-    __syncthreads();
-    if (t < II_TH) {
-      uint32_t corner = 0u;
-#pragma unroll
-      for (int k = 0; k < II_BT / 32; k++) corner += s_red[k];
-      s_left[t] = corner + s_lin[t] + (t >= 32 ? s_lin[31] : 0u);
+    for (int j = 0; j < 4; j++) c[j] = j < cols ? a.colsum[b * a.W + x + j] : 0u;
+    // lane r: row y0 + r's sums of the segments to the left, and the totals
+    // of the tiles above and to the left
+    uint32_t left = 0u, cv = 0u;
+    for (int64_t k = 0; k < s; k++) {
+      if (lane < rows) left += a.rowsum[k * a.H + y0 + lane];
+      for (int64_t bb = lane; bb < b; bb += 64) cv += a.total[bb * a.ns + k];
     }
+    uint32_t corner = (uint32_t)__builtin_amdgcn_readlane((int)ii_wave_scan(cv), 63);
+    const uint32_t above = ii_wave_scan(c[0] + c[1] + c[2] + c[3]);
+    if (lane == 63) s_above[w] = above;
+#pragma unroll
+    for (int r = 0; r < II_TH; r++)
+      if (r >= rows || cols == 0) px[r] = 0u;
+    uint32_t v[64];
+#pragma unroll
+    for (int r = 0; r < 64; r++) v[r] = __builtin_amdgcn_sad_u8(px[r], 0u, 0u);
+    // lane r ends with row r's sum: the halves kept at each step are chosen
+    // by the row's bits from the highest down
+    ii_halve<32, 32>(v, lane);
+    ii_halve<16, 16>(v, lane);
+    ii_halve<8, 8>(v, lane);
+    ii_halve<4, 4>(v, lane);
+    ii_halve<2, 2>(v, lane);
+    ii_halve<1, 1>(v, lane);
+    s_rt[w][lane] = v[0];
     __syncthreads();
-    // rounds of II_RS rows; the next round's pixels are requested before
-    // the current round's barrier and stores
-    uint32_t pn[II_RS][4];
 #pragma unroll
-    for (int r = 0; r < II_RS; r++) ii_pixels<VEC>(a, y0 + r, r < rows, x, pn[r]);
-    for (int r0 = 0; r0 < rows; r0 += II_RS) {
-      uint32_t q[II_RS][4];
-#pragma unroll
-      for (int r = 0; r < II_RS; r++) {
-#pragma unroll
-        for (int j = 0; j < 4; j++) c[j] += pn[r][j];
-        q[r][0] = c[0];
-        q[r][1] = q[r][0] + c[1];
-        q[r][2] = q[r][1] + c[2];
-        q[r][3] = q[r][2] + c[3];
-        const uint32_t incl = ii_warp_scan(q[r][3]);
-        const uint32_t excl = incl - q[r][3];
-#pragma unroll
-        for (int j = 0; j < 4; j++) q[r][j] += excl;
-        if (l == 31) s_wt[buf][r][w] = incl;
-      }
-#pragma unroll
-      for (int r = 0; r < II_RS; r++) {
-        const int rr = r0 + II_RS + r;
-        ii_pixels<VEC>(a, y0 + rr, rr < rows, x, pn[r]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < II_RS; r++) {
-        if (r0 + r >= rows) break;
-        uint32_t off = s_left[r0 + r];
-#pragma unroll
-        for (int k = 0; k < II_BT / 32; k++) off += k < w ? s_wt[buf][r][k] : 0u;
-        const int64_t y = y0 + r0 + r;
-        uint32_t *dst = a.sat + y * a.W + x;
-        if constexpr (VEC) {
-          // plain (cached) stores: the table is four times the image, and
-          // for write-dominated traffic they beat non-temporal stores
-          if (x < a.W) *(u32x4 *)dst = u32x4{q[r][0] + off, q[r][1] + off, q[r][2] + off, q[r][3] + off};
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; j++)
-            if (x + j < a.W) dst[j] = q[r][j] + off;
-        }
-      }
-      buf ^= 1;
+    for (int k = 0; k < 3; k++) {
+      left += k < w ? s_rt[k][lane] : 0u;
+      corner += k < w ? s_above[k] : 0u;
     }
-    __syncthreads();
+    left = corner + ii_wave_scan(left);
+    uint32_t *dst = a.sat + y0 * a.W + x;
+#pragma unroll
+    for (int r = 0; r < II_TH; r++) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) c[j] += (px[r] >> (8 * j)) & 0xffu;
+      uint32_t q[4];
+      q[0] = c[0];
+#pragma unroll
+      for (int j = 1; j < 4; j++) q[j] = q[j - 1] + c[j];
+      const uint32_t off = ii_wave_scan(q[3]) - q[3] + (uint32_t)__builtin_amdgcn_readlane((int)left, r);
+      // plain (cached) stores: the table is four times the image, and for
+      // write-dominated traffic they beat non-temporal stores
+      if constexpr (MODE == II_VEC) {
+        if (r < rows && cols) *(u32x4 *)dst = u32x4{q[0] + off, q[1] + off, q[2] + off, q[3] + off};
+      } else if (r < rows && cols == 4) {
+        *(ii_u32x4u *)dst = ii_u32x4u{q[0] + off, q[1] + off, q[2] + off, q[3] + off};
+      } else if (r < rows) {
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+          if (j < cols) dst[j] = q[j] + off;
+      }
+      dst += a.W;
+    }
+    __syncthreads();  // s_rt is written again for the next tile
   }
 }
 
@@ -423,8 +510,9 @@ extern "C" cox_status cox_integral_image(const uint8_t *img, int64_t height, int
   a.total = (uint32_t *)(w + L.total);
   const bool vec = width % 4 == 0 && ((uintptr_t)img & 3u) == 0 && aligned16(sat);
   const bool vec16 = width % 16 == 0 && ((uintptr_t)img & 15u) == 0;
-  auto reduce = vec16 ? k_ii_reduce16 : vec ? k_ii_reduce<true> : k_ii_reduce<false>;
-  auto scan = vec ? k_ii_scan<true> : k_ii_scan<false>;
+  auto reduce = vec16 ? k_ii_reduce16<II_VEC> : width >= 16 ? k_ii_reduce16<II_ANY>
+                : width >= 4 ? k_ii_reduce<II_ANY> : k_ii_reduce<II_NARROW>;
+  auto scan = vec ? k_ii_scan<II_VEC> : width >= 4 ? k_ii_scan<II_ANY> : k_ii_scan<II_NARROW>;
   hipStream_t hs = (hipStream_t)stream;
   const int64_t tiles = a.nb * a.ns;
   const int g1 = persistent_grid((const void *)reduce, II_BT, tiles, 0, 0, 8);
