@@ -490,8 +490,9 @@ cox_status cox_grid_exchange_absent(int32_t grid_blocks, int32_t rounds, int32_t
                                     uint32_t *out, void *ws, size_t ws_bytes, void *stream);
 
 /* Conjugate gradient (Hestenes and Stiefel) for A x = b, A symmetric
- * positive definite in CSR form, in ONE cooperative launch: the iteration
- * loop runs inside the kernel with two grid barriers per iteration.
+ * positive definite in CSR form, in ONE cooperative launch (an ordinary one
+ * if it has one block): the iteration loop runs inside the kernel with at
+ * most two grid barriers per iteration.
  *   row_ptr : device int32[n + 1], row_ptr[0] = 0, nondecreasing,
  *             row_ptr[n] = nnz;  col_idx : device int32[nnz] in [0, n);
  *   val     : device float[nnz];  b : device float[n];
@@ -518,8 +519,9 @@ cox_status cox_grid_exchange_absent(int32_t grid_blocks, int32_t rounds, int32_t
  * per block, x, r, p and q stay in registers for the whole solve, and a
  * block whose rows fit in what shared memory the grid leaves (at most
  * 65535 entries) reads its rows of row_ptr, col_idx and val once; if every
- * such block's columns lie within 64 rows of its chunk, the blocks exchange
- * only those halo rows of r and p through memory.
+ * such block's columns lie within 64 rows of its chunk, and there are at most
+ * 256 chunks, the blocks exchange only those halo rows of r and their shares
+ * of the inner products, as tagged words, without grid barriers.
  * cfg: items_per_lane 1, 2, 4 or 8, warps_per_block 8, 16 or 32
  * (COX_ERR_UNSUPPORTED otherwise), grid_blocks 0 = one block per compute
  * unit.  Malformed CSR (indices out of range) gives meaningless results

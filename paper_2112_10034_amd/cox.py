@@ -567,7 +567,8 @@ def cg_solve(row_ptr, col_idx, val, b, x, max_iter, tol=0.0, cfg=None, rr_hist=N
     if row_ptr.numel() != n + 1 or val.numel() != nnz or x.numel() != n:
         raise CoxError(1, "cg_solve: inconsistent CSR / vector sizes")
     dev = b.device
-    result = torch.zeros(2, dtype=torch.int32, device=dev) if result is None else result
+    # every solve writes both words of the result
+    result = torch.empty(2, dtype=torch.int32, device=dev) if result is None else result
     rr_hist = torch.zeros(max_iter + 1, dtype=torch.float64, device=dev) if rr_hist is None else rr_hist
     ws = workspace(OP_CG, F32, n, cfg=cfg)
     fn = lib().cox_cg_solve_per_phase if per_phase else lib().cox_cg_solve

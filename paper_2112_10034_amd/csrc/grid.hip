@@ -39,7 +39,8 @@
 // broadcast.  Chunk c belongs to block c mod G in every phase, so results do
 // not depend on G.  When every block holds at most one chunk, x, r, p and q
 // of the block's rows stay in registers for the whole solve and only r and
-// p (for the other blocks' gathers) and the partials are stored.
+// p (for the other blocks' gathers) and the partials are stored; if besides no
+// block reads beyond its halo, the barriers give way to tagged words (cg_near).
 #include <algorithm>
 
 #include "cox_internal.hpp"
@@ -184,6 +185,7 @@ struct CgShared {
   double slot[32];
   double fin[256];
   double bcast;
+  uint32_t ok;
   uint32_t elo, ehi;  // entry range of the chunk's rows (CSR staging)
   float win[32 * W * R + 2 * HALO];
 };
@@ -393,24 +395,17 @@ __device__ __forceinline__ void cg_phase0_chunk(const CgArgs &a, int64_t c, SH &
   chunk_store<W>(s, a.prr, c, sh);
 }
 
-// rows of chunk c that other chunks' windows read: the first and last HALO
-__device__ __forceinline__ bool halo_row(int64_t c, int32_t row, int S) {
-  const int64_t o = (int64_t)row - c * S;
-  return o < HALO || o >= S - HALO;
-}
-
 // p of the chunk's rows from the window into p[k & 1], partials of <p, q>
 template <int R, int W, class SH>
 __device__ __forceinline__ void cg_phase1_tail(const CgArgs &a, int64_t c, const int32_t (&row)[R], int32_t w0,
-                                               float *pn, SH &sh, float (&pv)[R], const float (&qv)[R],
-                                               bool near = false) {
+                                               float *pn, SH &sh, float (&pv)[R], const float (&qv)[R]) {
   double s = -0.0;
 #pragma unroll
   for (int q = 0; q < R; q++) {
     pv[q] = 0.0f;
     if (row[q] < a.n) {
       pv[q] = sh.win[row[q] - w0];
-      if (!near || halo_row(c, row[q], 32 * W * R)) stcf(pn + row[q], pv[q]);
+      stcf(pn + row[q], pv[q]);
       s = s + (double)pv[q] * (double)qv[q];
     }
   }
@@ -496,41 +491,10 @@ __device__ int cg_stage(const CgArgs &a, int64_t c, uint8_t *dyn, SH &sh) {
   return __syncthreads_or(outside) ? 1 : 2;
 }
 
-// p over chunk c's window when no block reads outside its window: the
-// chunk's own rows from the registers (p_prev, r), the HALO rows on each
-// side from the neighbours' stores; ends with a block barrier
-template <int R, int W, class SH>
-__device__ __forceinline__ int32_t cg_window_near(const CgArgs &a, int64_t c, bool first, float beta, const float *pp,
-                                                  const float (&pv)[R], const float (&rv)[R], SH &sh, int32_t &wn) {
-  constexpr int BT = 32 * W, S = BT * R;
-  const int64_t lo = c * S;
-  const int32_t w0 = (int32_t)(lo > HALO ? lo - HALO : 0);
-  const int32_t w1 = (int32_t)(lo + S + HALO < a.n ? lo + S + HALO : a.n);
-  const int t = threadIdx.x;
-  if (t < 2 * HALO) {
-    const int32_t j = t < HALO ? (int32_t)lo - HALO + t : (int32_t)(lo + S) + (t - HALO);
-    if (j >= w0 && j < w1) {
-      const float rj = ldcf(a.r + j);
-      sh.win[j - w0] = first ? rj : __builtin_fmaf(beta, ldcf(pp + j), rj);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < R; q++) {
-    const int32_t j = (int32_t)lo + BT * q + t;
-    if (j < a.n) sh.win[j - w0] = first ? rv[q] : __builtin_fmaf(beta, pv[q], rv[q]);
-  }
-  __syncthreads();
-  wn = w1 - w0;
-  return w0;
-}
-
-// phase 1 of the resident kernel on staged rows; near: no block reads
-// outside its window, so the window comes from registers and halos and
-// only the halo rows of p are stored
+// phase 1 of the resident kernel on staged rows
 template <int R, int W, class SH>
 __device__ __forceinline__ void cg_phase1_chunk_lds(const CgArgs &a, int64_t c, int k, float beta, SH &sh,
-                                                    const uint8_t *dyn, bool near, float (&pv)[R], float (&qv)[R],
-                                                    const float (&rv)[R]) {
+                                                    const uint8_t *dyn, float (&pv)[R], float (&qv)[R]) {
   constexpr int BT = 32 * W, S = BT * R;
   const bool first = k == 0;
   const float *pp = a.p[(k + 1) & 1];
@@ -538,8 +502,7 @@ __device__ __forceinline__ void cg_phase1_chunk_lds(const CgArgs &a, int64_t c, 
   int32_t row[R];
   rows_of<R, W>(c, row);
   int32_t wn;
-  const int32_t w0 = near ? cg_window_near<R, W>(a, c, first, beta, pp, pv, rv, sh, wn)
-                          : cg_window<R, W>(a, c, first, beta, pp, sh, wn);
+  const int32_t w0 = cg_window<R, W>(a, c, first, beta, pp, sh, wn);
   const uint32_t *bnd = (const uint32_t *)dyn;
   const uint2 *ent = (const uint2 *)(dyn + S * 4);
 #pragma unroll
@@ -560,14 +523,13 @@ __device__ __forceinline__ void cg_phase1_chunk_lds(const CgArgs &a, int64_t c, 
     }
     qv[q] = acc;
   }
-  cg_phase1_tail<R, W>(a, c, row, w0, pn, sh, pv, qv, near);
+  cg_phase1_tail<R, W>(a, c, row, w0, pn, sh, pv, qv);
 }
 
 // x = fmaf(alpha, p, x), r = fmaf(-alpha, q, r), partials of <r, r>
 template <int R, int W, class SH>
 __device__ __forceinline__ void cg_phase2_chunk(const CgArgs &a, int64_t c, float alpha, SH &sh, const float (&pv)[R],
-                                                const float (&qv)[R], float (&xv)[R], float (&rv)[R],
-                                                bool near = false) {
+                                                const float (&qv)[R], float (&xv)[R], float (&rv)[R]) {
   int32_t row[R];
   rows_of<R, W>(c, row);
   double s = -0.0;
@@ -576,7 +538,7 @@ __device__ __forceinline__ void cg_phase2_chunk(const CgArgs &a, int64_t c, floa
     if (row[q] < a.n) {
       xv[q] = __builtin_fmaf(alpha, pv[q], xv[q]);
       rv[q] = __builtin_fmaf(-alpha, qv[q], rv[q]);
-      if (!near || halo_row(c, row[q], 32 * W * R)) stcf(a.r + row[q], rv[q]);
+      stcf(a.r + row[q], rv[q]);
       s = s + (double)rv[q] * (double)rv[q];
     }
   }
@@ -670,6 +632,221 @@ __global__ __launch_bounds__(32 * W) void k_cg(CgArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- exchange of a near solve
+// When no block of the resident kernel reads outside its window (near), the
+// blocks need from each other only the r of the HALO rows next to theirs and
+// the two inner products.  Both then travel as tagged words [tag | 32 bits],
+// each polled by those who need it, and no grid barrier is left in the loop:
+//  - an inner product: block c publishes its chunk value (two words); the
+//    first block of every 32 chunks gathers them, runs their tree and
+//    publishes the group's value; every block polls the at most 8 group
+//    values (one line) and runs the last tree.  The trees are those of the
+//    FP64 final combine, so the result is bit for bit the same (the last
+//    tree of one group's value and seven -0.0 is that value);
+//  - the halo rows' r: a word each, polled by the neighbour's lanes.  Their p
+//    needs no exchange: a block forms it over its window with the owner's
+//    fmaf, from the p that it formed there in the iteration before.
+// What bounds an iteration is the chain of round trips between blocks: with
+// barriers it was two times store completion, three dependent atomics, the
+// generation poll and 256 loads (13.2 us at 256 blocks); now two times
+// publish, gather, publish, poll (6.4 us; 32 blocks 11.7 and 6.0, 2 blocks 9.7
+// and 4.4, one block 7.2 and 2.2).  (Every block polling all 256
+// chunk values is as slow as the barriers: 65536 polls on the same lines.)
+// A word is rewritten only one iteration later, after a product that needs
+// every reader's next contribution, so no reader can miss its tag.  The words
+// are cleared before the solve's first grid barrier.  They live in the
+// regions of p and q, which a near solve does not use.
+struct CgWords {
+  uint64_t *halo;     // [chunk][2 HALO]: r of the chunk's first and last HALO rows
+  uint64_t *pq, *rr;  // copies of the 16 group words, then 2 words per chunk
+};
+
+// Copies of the group values, a line each; block c polls copy c mod 8.  (All
+// 256 blocks polling one line: 8.0 us per iteration instead of 6.6.)  Up to
+// 16 chunks need no leader: every block gathers all chunk values (10 chunks:
+// 5.0 us per iteration against 6.2; at 32 it would be 6.4).
+__device__ __forceinline__ int cg_copies(const CgArgs &a) { return a.nch > 16 ? 8 : 0; }
+
+__device__ __forceinline__ CgWords cg_words(const CgArgs &a) {
+  CgWords w;
+  w.halo = (uint64_t *)a.p[0];
+  w.pq = (uint64_t *)a.q;
+  w.rr = w.pq + 16 * cg_copies(a) + (2 * a.nch + 15) / 16 * 16;
+  return w;
+}
+
+// waits for the tag; false: gave up, or another wait did
+__device__ __forceinline__ bool cg_poll(const uint64_t *p, uint32_t tag, const CgArgs &a, uint32_t &bits) {
+  uint64_t v = ld_dev(p);
+  uint32_t spins = 0;
+  while ((uint32_t)(v >> 32) != tag) {
+    if (++spins > GRID_MAX_SPIN || ((spins & 255u) == 0u && ldc32(&a.bar[GB_ABORT]) != 0u)) {
+      stc32(&a.bar[GB_ABORT], 1u);
+      stc32(&a.hdr[HDR_ERR], 1u);
+      return false;
+    }
+    v = ld_dev(p);
+  }
+  bits = (uint32_t)v;
+  return true;
+}
+
+// the double whose halves lanes 2l and 2l + 1 of the wave hold (high first);
+// -0.0 from lane m on.  Every lane of the wave calls this.
+__device__ __forceinline__ double cg_pair(uint32_t bits, int l, int m) {
+  const int hi = bperm((int)bits, 2 * l), lo = bperm((int)bits, 2 * l + 1);
+  return l < m ? __hiloint2double(hi, lo) : -0.0;
+}
+
+// the inner product of the threads' sums s over all chunks (at most 256),
+// the same value in every thread; false: a wait gave up
+template <int W, class SH>
+__device__ __forceinline__ bool cg_product(double s, int64_t c, uint32_t tag, uint64_t *words, const CgArgs &a, SH &sh,
+                                           double &out) {
+  const int t = threadIdx.x, l = t & 31;
+  s = tree64(s);
+  if (l == 0) sh.slot[t >> 5] = s;
+  __syncthreads();
+  if (t < 64) {
+    double v = tree64(l < W ? sh.slot[l] : -0.0);
+    bool ok = true;
+    if (a.nch > 1) {
+      const uint64_t hi = (uint64_t)tag << 32;
+      auto half = [&](double d) { return (t & 1) ? (uint32_t)__double2loint(d) : (uint32_t)__double2hiint(d); };
+      const int copies = cg_copies(a);
+      uint64_t *const part = words + 16 * copies;
+      if (t < 2) st_dev(&part[2 * c + t], hi | half(v));
+      const bool direct = copies == 0;
+      if (direct || (c & 31) == 0) {
+        const int64_t c0 = direct ? 0 : c;
+        const int m = a.nch - c0 < 32 ? (int)(a.nch - c0) : 32;
+        uint32_t bits = 0u;
+        if (t < 2 * m) ok = cg_poll(&part[2 * c0 + t], tag, a, bits);
+        v = tree64(cg_pair(bits, l, m));
+        // a group whose chunk values did not all arrive is not published
+        if (!direct && __builtin_amdgcn_ballot_w64(!ok) == 0 && t < 2 * copies)
+          st_dev(&words[(t >> 1) * 16 + (c >> 5) * 2 + (t & 1)], hi | half(v));
+      }
+      if (!direct) {
+        const int ng = (int)((a.nch + 31) >> 5);
+        uint32_t bits = 0u;
+        if (t < 2 * ng) ok = cg_poll(&words[(c & 7) * 16 + t], tag, a, bits) && ok;
+        v = tree64(cg_pair(bits, l, ng));
+      }
+    }
+    const bool bad = __builtin_amdgcn_ballot_w64(!ok) != 0;
+    if (t == 0) {
+      sh.bcast = v;
+      sh.ok = bad ? 0u : 1u;
+    }
+  }
+  __syncthreads();
+  out = sh.bcast;
+  return sh.ok != 0u;
+}
+
+// clears this block's words (chunk c; ahead of a grid barrier)
+__device__ __forceinline__ void cg_words_clear(const CgArgs &a, int64_t c) {
+  if (a.nch < 2) return;
+  const CgWords w = cg_words(a);
+  const int t = threadIdx.x, copies = cg_copies(a);
+  if (t < 2 * HALO) st_dev(&w.halo[c * (2 * HALO) + t], 0u);
+  if (t < 2) {
+    st_dev(&w.pq[16 * copies + 2 * c + t], 0u);
+    st_dev(&w.rr[16 * copies + 2 * c + t], 0u);
+  }
+  if (c == 0 && t < 16 * copies) {
+    st_dev(&w.pq[t], 0u);
+    st_dev(&w.rr[t], 0u);
+  }
+}
+
+// the iterations of a near solve from rr_0 on; returns the reason, k by
+// reference.  Iteration k's words carry the tag k + 1.
+template <int R, int W, class SH>
+__device__ int32_t cg_near(const CgArgs &a, int64_t c, SH &sh, const uint8_t *dyn, double rr, float (&xv)[R],
+                           float (&rv)[R], int32_t &k) {
+  constexpr int BT = 32 * W, S = BT * R;
+  static_assert(S >= 2 * HALO && BT >= 2 * HALO, "a row is in at most one halo; a lane per halo row");
+  const CgWords words = cg_words(a);
+  const int t = threadIdx.x;
+  const int64_t lo = c * S;
+  const int32_t w0 = (int32_t)(lo > HALO ? lo - HALO : 0);
+  const int32_t w1 = (int32_t)(lo + S + HALO < a.n ? lo + S + HALO : a.n);
+  // halo row j of this lane (its owner's word: the last rows of the chunk
+  // before, the first of the one after)
+  const int32_t hj = t < HALO ? (int32_t)(lo - HALO) + t : (int32_t)(lo + S) + (t - HALO);
+  const bool halo = t < 2 * HALO && hj >= w0 && hj < w1 && (t < HALO ? lo > 0 : true);
+  const uint64_t *const hword = words.halo + (t < HALO ? (c - 1) * (2 * HALO) + HALO + t : (c + 1) * (2 * HALO) + t - HALO);
+  const uint32_t *bnd = (const uint32_t *)dyn;
+  const uint2 *ent = (const uint2 *)(dyn + S * 4);
+  float pv[R], qv[R];
+  double rr_prev = 0.0;
+  for (;; k++) {
+    if (lead() && a.rr_hist) a.rr_hist[k] = rr;
+    if (rr <= a.tol2) return CG_CONVERGED;
+    if (k == a.max_iter) return CG_MAX_ITER;
+    const bool first = k == 0;
+    const float beta = first ? 0.0f : (float)(rr / rr_prev);
+    const uint32_t tag = (uint32_t)k + 1u;
+    // p over the window
+    int lost = 0;
+    if (halo) {
+      uint32_t bits = 0u;
+      float rj;
+      if (first) {
+        rj = ldcf(a.r + hj);  // stored by phase 0, ahead of the grid barrier
+      } else {
+        lost = !cg_poll(hword, tag - 1u, a, bits);
+        rj = i2f((int)bits);
+      }
+      sh.win[hj - w0] = first ? rj : __builtin_fmaf(beta, sh.win[hj - w0], rj);
+    }
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+      const int32_t j = (int32_t)lo + BT * q + t;
+      pv[q] = 0.0f;
+      if (j < a.n) {
+        pv[q] = first ? rv[q] : __builtin_fmaf(beta, sh.win[j - w0], rv[q]);
+        sh.win[j - w0] = pv[q];
+      }
+    }
+    if (__syncthreads_or(lost)) return CG_ABORTED;
+    // q = A p, <p, q>
+    double s = -0.0;
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+      const uint32_t bq = bnd[BT * q + t];
+      float acc = 0.0f;
+      for (uint32_t e = bq & 0xffffu; e < (bq >> 16); e++) {
+        const uint2 ev = ent[e];
+        acc = __builtin_fmaf(__uint_as_float(ev.y), sh.win[ev.x - (uint32_t)w0], acc);
+      }
+      qv[q] = acc;
+      if ((int32_t)lo + BT * q + t < a.n) s = s + (double)pv[q] * (double)acc;
+    }
+    double pq;
+    if (!cg_product<W>(s, c, tag, words.pq, a, sh, pq)) return CG_ABORTED;
+    if (!(pq > 0.0)) return CG_BREAKDOWN;
+    const float alpha = (float)(rr / pq);
+    s = -0.0;
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+      const int32_t o = BT * q + t;
+      if ((int32_t)lo + o < a.n) {
+        xv[q] = __builtin_fmaf(alpha, pv[q], xv[q]);
+        rv[q] = __builtin_fmaf(-alpha, qv[q], rv[q]);
+        if (a.nch > 1 && (o < HALO || o >= S - HALO))
+          st_dev(&words.halo[c * (2 * HALO) + (o < HALO ? o : o - (S - 2 * HALO))],
+                 ((uint64_t)tag << 32) | (uint32_t)f2i(rv[q]));
+        s = s + (double)rv[q] * (double)rv[q];
+      }
+    }
+    rr_prev = rr;
+    if (!cg_product<W>(s, c, tag, words.rr, a, sh, rr)) return CG_ABORTED;
+  }
+}
+
 // the same solve with at most one chunk per block (gridDim.x >= nch): the
 // block's x, r, p and q stay in registers, its CSR rows in shared memory
 // when they fit; x is stored once at the end
@@ -686,12 +863,16 @@ __global__ __launch_bounds__(32 * W) void k_cg_res(CgArgs a) {
   // a block that streams its rows or gathers outside its window needs
   // every row of r and p in memory
   if (stage < 2 && threadIdx.x == 0) __hip_atomic_fetch_or(&a.state->far, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (own) cg_phase0_chunk<R, W, su_resident<R>()>(a, c, sh, xv, rv);
+  if (own) {
+    cg_words_clear(a, c);
+    cg_phase0_chunk<R, W, su_resident<R>()>(a, c, sh, xv, rv);
+  }
   if (grid_sync(a.bar, a.hdr)) {
     // the same word for every thread, written before the barrier
-    const bool near = staged && ldc32(&a.state->far) == 0u;
+    const bool near = staged && a.nch <= 256 && ldc32(&a.state->far) == 0u;
     double rr = final64(a.prr, a.nch, sh), rr_prev = 0.0;
-    for (;; k++) {
+    if (near) reason = cg_near<R, W>(a, c, sh, cg_dyn, rr, xv, rv, k);
+    else for (;; k++) {
       if (lead() && a.rr_hist) a.rr_hist[k] = rr;
       if (rr <= a.tol2) {
         reason = CG_CONVERGED;
@@ -703,7 +884,7 @@ __global__ __launch_bounds__(32 * W) void k_cg_res(CgArgs a) {
       }
       const float beta = k ? (float)(rr / rr_prev) : 0.0f;
       if (staged)
-        cg_phase1_chunk_lds<R, W>(a, c, k, beta, sh, cg_dyn, near, pv, qv, rv);
+        cg_phase1_chunk_lds<R, W>(a, c, k, beta, sh, cg_dyn, pv, qv);
       else if (own)
         cg_phase1_chunk<R, W, su_resident<R>()>(a, c, k, beta, sh, pv, qv);
       if (!grid_sync(a.bar, a.hdr)) break;
@@ -712,7 +893,7 @@ __global__ __launch_bounds__(32 * W) void k_cg_res(CgArgs a) {
         reason = CG_BREAKDOWN;
         break;
       }
-      if (own) cg_phase2_chunk<R, W>(a, c, (float)(rr / pq), sh, pv, qv, xv, rv, near);
+      if (own) cg_phase2_chunk<R, W>(a, c, (float)(rr / pq), sh, pv, qv, xv, rv);
       if (!grid_sync(a.bar, a.hdr)) break;
       rr_prev = rr;
       rr = final64(a.prr, a.nch, sh);
@@ -911,8 +1092,11 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   if ((st = launch_status()) != COX_OK) return st;
   if (coop) {
     // one chunk per block at most: the register-resident kernel
+    // (a grid of one block is resident without a cooperative launch, whose
+    // own queue costs some tens of microseconds per call)
     void *args[] = {&a};
-    const hipError_t e = hipLaunchCooperativeKernel(fn, dim3(G), dim3(block), args, a.lds_bytes, hs);
+    const hipError_t e = G == 1 ? hipLaunchKernel(fn, dim3(1), dim3(block), args, a.lds_bytes, hs)
+                                : hipLaunchCooperativeKernel(fn, dim3(G), dim3(block), args, a.lds_bytes, hs);
     if (e != hipSuccess) {
       set_hip_error(e);
       return COX_ERR_HIP;
