@@ -965,6 +965,13 @@ typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
 // wholly past e1 reads x[0..3] instead (one line for all such lanes).  The
 // one vector that would reach past the end of x is read element by element
 // afterwards.  x of fewer than four elements is read element by element.
+//
+// All loads of x are ordinary ones, not streaming ones: a segment starts at
+// any 4-byte address, so most vectors of a wave share their first and last
+// cache line with the next row's, the next warp's or the next segment's
+// load, and a line marked as streamed was often gone by then.  A fused
+// call over 10,000 segments took 318 us (FP32 335) with streaming loads,
+// 302 (321) with these; 3,000 segments 123 (129) against 118.5 (125).
 template <int R, int V, int DT>
 __device__ __forceinline__ void seg_load_part(const uint32_t *__restrict__ x, int64_t n, int64_t wbase,
                                               int64_t e1, int l, uint32_t (&v)[R][V]) {
@@ -976,7 +983,7 @@ __device__ __forceinline__ void seg_load_part(const uint32_t *__restrict__ x, in
 #pragma unroll
       for (int i = 0; i < R; i++) {
         const int64_t e = e0 + i * 128;
-        q[i] = __builtin_nontemporal_load((const u32x4u *)(x + (e < e1 && e + 4 <= n ? e : 0)));
+        q[i] = *(const u32x4u *)(x + (e < e1 && e + 4 <= n ? e : 0));
       }
 #pragma unroll
       for (int i = 0; i < R; i++) {
@@ -1002,7 +1009,7 @@ __device__ __forceinline__ void seg_load_part(const uint32_t *__restrict__ x, in
   for (int i = 0; i < R; i++) {
     const int64_t e = wbase + (int64_t)(i * 32 + l) * V;
 #pragma unroll
-    for (int j = 0; j < V; j++) v[i][j] = e + j < e1 ? ld_stream1(x + e + j) : I;
+    for (int j = 0; j < V; j++) v[i][j] = e + j < e1 ? x[e + j] : I;
   }
 }
 
@@ -1143,13 +1150,13 @@ __global__ __launch_bounds__(1024) void k_segmented(const uint32_t *__restrict__
       for (int i = 0; i < R; i++) {
         const uint32_t *p = src + i * 32 * V;
         if constexpr (V == 4) {
-          const u32x4u q = __builtin_nontemporal_load((const u32x4u *)p);
+          const u32x4u q = *(const u32x4u *)p;
           v[i][0] = q.x; v[i][1] = q.y; v[i][2] = q.z; v[i][3] = q.w;
         } else if constexpr (V == 2) {
-          const u32x2u q = __builtin_nontemporal_load((const u32x2u *)p);
+          const u32x2u q = *(const u32x2u *)p;
           v[i][0] = q.x; v[i][1] = q.y;
         } else {
-          v[i][0] = ld_stream1(p);
+          v[i][0] = *p;
         }
       }
     } else {
