@@ -187,15 +187,29 @@ struct CgShared {
   double bcast;
   uint32_t ok;
   uint32_t elo, ehi;  // entry range of the chunk's rows (CSR staging)
-  float win[32 * W * R + 2 * HALO];
+  float win[32 * W * R + 2 * HALO + 1];  // and a zero (cg_near)
 };
 
 // xor butterfly over a logical warp: every lane ends with the value lane 0
 // of the shfl_down tree (offsets 16 .. 1) holds
+//
+// All five steps are VALU moves, none a ds_swizzle: offset 16 by
+// v_permlane16_swap of v with itself (each row's value beside its
+// partner's, in one order or the other), offset 4 by a rotation, since
+// lanes l and l + 8 of a row are equal by then.
+__device__ __forceinline__ double ror4_d(double v) {
+  int2 p = __builtin_bit_cast(int2, v);
+  p.x = dpp_mov<0x124>(p.x);
+  p.y = dpp_mov<0x124>(p.y);
+  return __builtin_bit_cast(double, p);
+}
 __device__ __forceinline__ double tree64(double v) {
-  v = v + xor_lane_d<16>(v);
+  const uint2 p = __builtin_bit_cast(uint2, v);
+  const auto x = __builtin_amdgcn_permlane16_swap(p.x, p.x, false, false);
+  const auto y = __builtin_amdgcn_permlane16_swap(p.y, p.y, false, false);
+  v = __hiloint2double((int)y[0], (int)x[0]) + __hiloint2double((int)y[1], (int)x[1]);
   v = v + xor_lane_d<8>(v);
-  v = v + xor_lane_d<4>(v);
+  v = v + ror4_d(v);
   v = v + xor_lane_d<2>(v);
   v = v + xor_lane_d<1>(v);
   return v;
@@ -637,41 +651,48 @@ __global__ __launch_bounds__(32 * W) void k_cg(CgArgs a) {
 // blocks need from each other only the r of the HALO rows next to theirs and
 // the two inner products.  Both then travel as tagged words [tag | 32 bits],
 // each polled by those who need it, and no grid barrier is left in the loop:
-//  - an inner product: block c publishes its chunk value (two words); the
-//    first block of every 32 chunks gathers them, runs their tree and
-//    publishes the group's value; every block polls the at most 8 group
-//    values (one line) and runs the last tree.  The trees are those of the
-//    FP64 final combine, so the result is bit for bit the same (the last
-//    tree of one group's value and seven -0.0 is that value);
-//  - the halo rows' r: a word each, polled by the neighbour's lanes.  Their p
-//    needs no exchange: a block forms it over its window with the owner's
-//    fmaf, from the p that it formed there in the iteration before.
-// What bounds an iteration is the chain of round trips between blocks: with
-// barriers it was two times store completion, three dependent atomics, the
-// generation poll and 256 loads (13.2 us at 256 blocks); now two times
-// publish, gather, publish, poll (6.4 us; 32 blocks 11.7 and 6.0, 2 blocks 9.7
-// and 4.4, one block 7.2 and 2.2).  (Every block polling all 256
-// chunk values is as slow as the barriers: 65536 polls on the same lines.)
+//  - an inner product: block c publishes its chunk value (two words) in 8
+//    copies; every block polls all values of one copy, a wave per 32 chunks,
+//    and runs the trees of the FP64 final combine itself, so the result is bit
+//    for bit the same;
+//  - the halo rows' r: a word each, polled by the neighbour's lanes while the
+//    values of <r, r> travel.  Their p needs no exchange: a block forms it
+//    over its window with the owner's fmaf, from the p that it formed there in
+//    the iteration before.
+// What bounds an iteration is twice a store's way to memory and a poll's round
+// trip, each about 1000 cycles, and between them the block's own chain of
+// window, gathers, FP64 trees and quotients (3700 cycles, most of them latency
+// at 4 waves per SIMD).  At 4096 rows per block, 256 / 32 / 10 / 2 / 1 blocks
+// take 4.0 / 3.7 / 3.7 / 3.2 / 1.5 us per iteration; with a leader per 32
+// chunks that gathers and publishes for the rest (two more trips per product),
+// entries read from shared memory, and the halo polled after the product it
+// took 7.9 / 6.3 / 5.4 / 4.8 / 2.2, with grid barriers 13.2 us at 256.
 // A word is rewritten only one iteration later, after a product that needs
 // every reader's next contribution, so no reader can miss its tag.  The words
 // are cleared before the solve's first grid barrier.  They live in the
 // regions of p and q, which a near solve does not use.
 struct CgWords {
   uint64_t *halo;     // [chunk][2 HALO]: r of the chunk's first and last HALO rows
-  uint64_t *pq, *rr;  // copies of the 16 group words, then 2 words per chunk
+  uint64_t *pq, *rr;  // [copy][chunk][2]: the halves of the chunk's value
 };
 
-// Copies of the group values, a line each; block c polls copy c mod 8.  (All
-// 256 blocks polling one line: 8.0 us per iteration instead of 6.6.)  Up to
-// 16 chunks need no leader: every block gathers all chunk values (10 chunks:
-// 5.0 us per iteration against 6.2; at 32 it would be 6.4).
-__device__ __forceinline__ int cg_copies(const CgArgs &a) { return a.nch > 16 ? 8 : 0; }
+// Copies of the chunk values, whole lines each; block c polls copy c mod 8 (at
+// 256 blocks 2 / 4 / 8 / 16 copies: 6.5 / 6.3 / 6.2 / 6.5 us per iteration,
+// before the wait ahead of the first poll).  The words of at most 4
+// chunks fit in the regions of the smallest such system only once.
+__device__ __forceinline__ int cg_copies(const CgArgs &a) { return a.nch > 4 ? 8 : 1; }
+// words of one copy, whole lines
+__device__ __forceinline__ int64_t cg_copy_words(const CgArgs &a) { return (2 * a.nch + 15) / 16 * 16; }
 
+// p[0], p[1] and q are consecutive, 12 n bytes or more.  The words take 1024
+// bytes per chunk for the halos and 128 (copies 8) or 16 bytes times
+// cg_copy_words for the products; with n > 256 (nch - 1) that is within
+// 12 n from two chunks (copies 1) and five chunks (copies 8) on.
 __device__ __forceinline__ CgWords cg_words(const CgArgs &a) {
   CgWords w;
   w.halo = (uint64_t *)a.p[0];
-  w.pq = (uint64_t *)a.q;
-  w.rr = w.pq + 16 * cg_copies(a) + (2 * a.nch + 15) / 16 * 16;
+  w.pq = w.halo + a.nch * (2 * HALO);
+  w.rr = w.pq + cg_copies(a) * cg_copy_words(a);
   return w;
 }
 
@@ -699,77 +720,94 @@ __device__ __forceinline__ double cg_pair(uint32_t bits, int l, int m) {
 }
 
 // the inner product of the threads' sums s over all chunks (at most 256),
-// the same value in every thread; false: a wait gave up
-template <int W, class SH>
-__device__ __forceinline__ bool cg_product(double s, int64_t c, uint32_t tag, uint64_t *words, const CgArgs &a, SH &sh,
-                                           double &out) {
-  const int t = threadIdx.x, l = t & 31;
+// the same value in every thread; false: a wait gave up.  mine: this lane's
+// word of the block's value; theirs: the copy that this block polls.
+// beside() runs while the chunk values travel.
+template <int W, class SH, class F>
+__device__ __forceinline__ bool cg_product(double s, uint32_t tag, uint64_t *mine, const uint64_t *theirs, int nch,
+                                           int copies, const CgArgs &a, SH &sh, double &out, F beside) {
+  constexpr int NW = W / 2;  // waves
+  const int t = threadIdx.x, l = t & 31, lane = t & 63, wave = t >> 6;
+  const int ng = (nch + 31) >> 5;
   s = tree64(s);
   if (l == 0) sh.slot[t >> 5] = s;
   __syncthreads();
-  if (t < 64) {
-    double v = tree64(l < W ? sh.slot[l] : -0.0);
-    bool ok = true;
-    if (a.nch > 1) {
-      const uint64_t hi = (uint64_t)tag << 32;
-      auto half = [&](double d) { return (t & 1) ? (uint32_t)__double2loint(d) : (uint32_t)__double2hiint(d); };
-      const int copies = cg_copies(a);
-      uint64_t *const part = words + 16 * copies;
-      if (t < 2) st_dev(&part[2 * c + t], hi | half(v));
-      const bool direct = copies == 0;
-      if (direct || (c & 31) == 0) {
-        const int64_t c0 = direct ? 0 : c;
-        const int m = a.nch - c0 < 32 ? (int)(a.nch - c0) : 32;
-        uint32_t bits = 0u;
-        if (t < 2 * m) ok = cg_poll(&part[2 * c0 + t], tag, a, bits);
-        v = tree64(cg_pair(bits, l, m));
-        // a group whose chunk values did not all arrive is not published
-        if (!direct && __builtin_amdgcn_ballot_w64(!ok) == 0 && t < 2 * copies)
-          st_dev(&words[(t >> 1) * 16 + (c >> 5) * 2 + (t & 1)], hi | half(v));
-      }
-      if (!direct) {
-        const int ng = (int)((a.nch + 31) >> 5);
-        uint32_t bits = 0u;
-        if (t < 2 * ng) ok = cg_poll(&words[(c & 7) * 16 + t], tag, a, bits) && ok;
-        v = tree64(cg_pair(bits, l, ng));
-      }
+  if (wave == NW - 2) {
+    const double v = tree64(l < W ? sh.slot[l] : -0.0);
+    const uint64_t word = (uint64_t)tag << 32 | ((t & 1) ? (uint32_t)__double2loint(v) : (uint32_t)__double2hiint(v));
+    if (nch == 1) {
+      if (lane == 0) sh.fin[0] = v;
+    } else if (lane < 2 * copies) {
+      st_dev(mine, word);
     }
-    const bool bad = __builtin_amdgcn_ballot_w64(!ok) != 0;
-    if (t == 0) {
-      sh.bcast = v;
-      sh.ok = bad ? 0u : 1u;
+  }
+  if (nch > 1) {
+    beside();
+    // A poll that comes before the words is paid for twice: it returns
+    // only after a round trip, and all blocks' early polls are in the
+    // stores' way.  So the waves wait first, for about as long as the
+    // publishing wave and its stores take (units of 64 cycles; us per
+    // iteration for waits of 0 / 8 / 12 / 14 / 17 / 20: 256 blocks 5.6 / 4.4 /
+    // 4.2 / 4.0 / 4.1 / 4.3, 32 blocks 4.1 / 3.8 / 3.7 / 3.7 / 3.8 / 3.9).
+    // Few blocks publish sooner and disturb less: two take 3.2 with 6, 3.5
+    // with 14.  (Several polls in flight, a part of a trip apart, were slower:
+    // 256 blocks 6.0 with two, 6.6 with four, against 5.6.)
+    if (nch > 4) __builtin_amdgcn_s_sleep(14);
+    else __builtin_amdgcn_s_sleep(6);
+    // a wave polls the words of chunks 32 g .. 32 g + 31
+    for (int g = (wave + NW - 2) % NW; g < ng; g += NW) {
+      const int m = nch - 32 * g < 32 ? nch - 32 * g : 32;
+      uint32_t bits = 0u;
+      bool ok = true;
+      if (lane < 2 * m) ok = cg_poll(theirs + 64 * g + lane, tag, a, bits);
+      const double v = tree64(cg_pair(bits, l, m));
+      if (lane == 0) sh.fin[g] = v;
+      if (!ok) sh.ok = 0u;
     }
   }
   __syncthreads();
-  out = sh.bcast;
-  return sh.ok != 0u;
+  // the tree over the group values (the first two of its five steps only
+  // add the -0.0 of lanes 8 to 31)
+  double v = (l & 7) < ng ? sh.fin[l & 7] : -0.0;
+  const bool ok = sh.ok != 0u;
+  v = v + ror4_d(v);
+  v = v + xor_lane_d<2>(v);
+  v = v + xor_lane_d<1>(v);
+  out = v;
+  return ok;
 }
 
 // clears this block's words (chunk c; ahead of a grid barrier)
 __device__ __forceinline__ void cg_words_clear(const CgArgs &a, int64_t c) {
   if (a.nch < 2) return;
   const CgWords w = cg_words(a);
-  const int t = threadIdx.x, copies = cg_copies(a);
+  const int t = threadIdx.x;
   if (t < 2 * HALO) st_dev(&w.halo[c * (2 * HALO) + t], 0u);
-  if (t < 2) {
-    st_dev(&w.pq[16 * copies + 2 * c + t], 0u);
-    st_dev(&w.rr[16 * copies + 2 * c + t], 0u);
-  }
-  if (c == 0 && t < 16 * copies) {
-    st_dev(&w.pq[t], 0u);
-    st_dev(&w.rr[t], 0u);
+  if (t < 2 * cg_copies(a)) {
+    const int64_t at = (t >> 1) * cg_copy_words(a) + 2 * c + (t & 1);
+    st_dev(&w.pq[at], 0u);
+    st_dev(&w.rr[at], 0u);
   }
 }
 
+// entries per row that a near solve holds in registers (4 against 1 at R = 4,
+// W = 32: 5.8 and 6.1 us per iteration, before the other changes)
+template <int R>
+constexpr int cg_held() {
+  return R >= 8 ? 2 : 4;
+}
+
 // the iterations of a near solve from rr_0 on; returns the reason, k by
-// reference.  Iteration k's words carry the tag k + 1.
+// reference.  Iteration k's words carry the tag k + 1.  Rows past n of the
+// last chunk run along without branches: their p is +0 and their q -0, so
+// that they add -0.0 to <p, q>; their r is +0.
 template <int R, int W, class SH>
 __device__ int32_t cg_near(const CgArgs &a, int64_t c, SH &sh, const uint8_t *dyn, double rr, float (&xv)[R],
                            float (&rv)[R], int32_t &k) {
-  constexpr int BT = 32 * W, S = BT * R;
+  constexpr int BT = 32 * W, S = BT * R, ZERO = S + 2 * HALO;
   static_assert(S >= 2 * HALO && BT >= 2 * HALO, "a row is in at most one halo; a lane per halo row");
   const CgWords words = cg_words(a);
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, nch = (int)a.nch, copies = cg_copies(a);
   const int64_t lo = c * S;
   const int32_t w0 = (int32_t)(lo > HALO ? lo - HALO : 0);
   const int32_t w1 = (int32_t)(lo + S + HALO < a.n ? lo + S + HALO : a.n);
@@ -778,72 +816,106 @@ __device__ int32_t cg_near(const CgArgs &a, int64_t c, SH &sh, const uint8_t *dy
   const int32_t hj = t < HALO ? (int32_t)(lo - HALO) + t : (int32_t)(lo + S) + (t - HALO);
   const bool halo = t < 2 * HALO && hj >= w0 && hj < w1 && (t < HALO ? lo > 0 : true);
   const uint64_t *const hword = words.halo + (t < HALO ? (c - 1) * (2 * HALO) + HALO + t : (c + 1) * (2 * HALO) + t - HALO);
-  const uint32_t *bnd = (const uint32_t *)dyn;
+  const int64_t my = (lane >> 1) * cg_copy_words(a) + 2 * c + (t & 1), copy = (c & (copies - 1)) * cg_copy_words(a);
   const uint2 *ent = (const uint2 *)(dyn + S * 4);
-  float pv[R], qv[R];
-  double rr_prev = 0.0;
+  // the rows' first NU entries stay in registers, as byte offsets of the
+  // window's elements and values; an absent one is the window's zero word
+  // times -0.0, which leaves any sum as it is
+  constexpr int NU = cg_held<R>();
+  uint32_t e0[R], len[R], more = 0u;
+  uint32_t eo[NU][R];
+  float ev[NU][R];
+#pragma unroll
+  for (int q = 0; q < R; q++) {
+    const uint32_t bq = ((const uint32_t *)dyn)[BT * q + t];
+    e0[q] = bq & 0xffffu;
+    len[q] = (bq >> 16) - e0[q];
+    more = max(more, len[q]);
+#pragma unroll
+    for (int u = 0; u < NU; u++) {
+      const bool held = u < (int)len[q];
+      const uint2 e = ent[held ? e0[q] + u : 0];
+      eo[u][q] = held ? 4u * (e.x - (uint32_t)w0) : 4u * ZERO;
+      ev[u][q] = held ? __uint_as_float(e.y) : -0.0f;
+    }
+  }
+  float pv[R], qv[R], hp = -0.0f;
+  float hr = halo ? ldcf(a.r + hj) : 0.0f;  // stored by phase 0, ahead of the grid barrier
+#pragma unroll
+  for (int q = 0; q < R; q++) pv[q] = -0.0f;  // p_0 = fmaf(0, -0, r) = r
+  float beta = 0.0f;
+  if (t == 0) {
+    sh.ok = 1u;
+    sh.win[ZERO] = 0.0f;
+  }
+  __syncthreads();
+  const int32_t rows = a.n - (int32_t)lo - t;  // row q of the thread exists if BT q < rows
   for (;; k++) {
-    if (lead() && a.rr_hist) a.rr_hist[k] = rr;
+    if (c == 0 && t == BT - 1 && a.rr_hist) a.rr_hist[k] = rr;
     if (rr <= a.tol2) return CG_CONVERGED;
     if (k == a.max_iter) return CG_MAX_ITER;
-    const bool first = k == 0;
-    const float beta = first ? 0.0f : (float)(rr / rr_prev);
     const uint32_t tag = (uint32_t)k + 1u;
     // p over the window
-    int lost = 0;
     if (halo) {
-      uint32_t bits = 0u;
-      float rj;
-      if (first) {
-        rj = ldcf(a.r + hj);  // stored by phase 0, ahead of the grid barrier
-      } else {
-        lost = !cg_poll(hword, tag - 1u, a, bits);
-        rj = i2f((int)bits);
-      }
-      sh.win[hj - w0] = first ? rj : __builtin_fmaf(beta, sh.win[hj - w0], rj);
+      hp = __builtin_fmaf(beta, hp, hr);
+      sh.win[hj - w0] = hp;
     }
+    float *const own = sh.win + ((int32_t)lo - w0) + t;
 #pragma unroll
     for (int q = 0; q < R; q++) {
-      const int32_t j = (int32_t)lo + BT * q + t;
-      pv[q] = 0.0f;
-      if (j < a.n) {
-        pv[q] = first ? rv[q] : __builtin_fmaf(beta, sh.win[j - w0], rv[q]);
-        sh.win[j - w0] = pv[q];
-      }
+      const float pn = __builtin_fmaf(beta, pv[q], rv[q]);
+      pv[q] = BT * q < rows ? pn : 0.0f;
+      own[BT * q] = pv[q];
     }
-    if (__syncthreads_or(lost)) return CG_ABORTED;
-    // q = A p, <p, q>
+    __syncthreads();
+    // q = A p, <p, q>; the rows' gathers are in flight together
+    float g[NU][R];
+#pragma unroll
+    for (int u = 0; u < NU; u++)
+#pragma unroll
+      for (int q = 0; q < R; q++) g[u][q] = *(const float *)((const uint8_t *)sh.win + eo[u][q]);
+#pragma unroll
+    for (int q = 0; q < R; q++) qv[q] = BT * q < rows ? 0.0f : -0.0f;
+#pragma unroll
+    for (int u = 0; u < NU; u++)
+#pragma unroll
+      for (int q = 0; q < R; q++) qv[q] = __builtin_fmaf(ev[u][q], g[u][q], qv[q]);
+    if (more > NU)
+#pragma unroll
+      for (int q = 0; q < R; q++)
+        for (uint32_t u = NU; u < len[q]; u++) {
+          const uint2 e = ent[e0[q] + u];
+          qv[q] = __builtin_fmaf(__uint_as_float(e.y), sh.win[e.x - (uint32_t)w0], qv[q]);
+        }
     double s = -0.0;
 #pragma unroll
-    for (int q = 0; q < R; q++) {
-      const uint32_t bq = bnd[BT * q + t];
-      float acc = 0.0f;
-      for (uint32_t e = bq & 0xffffu; e < (bq >> 16); e++) {
-        const uint2 ev = ent[e];
-        acc = __builtin_fmaf(__uint_as_float(ev.y), sh.win[ev.x - (uint32_t)w0], acc);
-      }
-      qv[q] = acc;
-      if ((int32_t)lo + BT * q + t < a.n) s = s + (double)pv[q] * (double)acc;
-    }
+    for (int q = 0; q < R; q++) s = s + (double)pv[q] * (double)qv[q];
     double pq;
-    if (!cg_product<W>(s, c, tag, words.pq, a, sh, pq)) return CG_ABORTED;
+    if (!cg_product<W>(s, tag, words.pq + my, words.pq + copy, nch, copies, a, sh, pq, [] {})) return CG_ABORTED;
     if (!(pq > 0.0)) return CG_BREAKDOWN;
     const float alpha = (float)(rr / pq);
     s = -0.0;
 #pragma unroll
     for (int q = 0; q < R; q++) {
-      const int32_t o = BT * q + t;
-      if ((int32_t)lo + o < a.n) {
-        xv[q] = __builtin_fmaf(alpha, pv[q], xv[q]);
-        rv[q] = __builtin_fmaf(-alpha, qv[q], rv[q]);
-        if (a.nch > 1 && (o < HALO || o >= S - HALO))
-          st_dev(&words.halo[c * (2 * HALO) + (o < HALO ? o : o - (S - 2 * HALO))],
-                 ((uint64_t)tag << 32) | (uint32_t)f2i(rv[q]));
-        s = s + (double)rv[q] * (double)rv[q];
-      }
+      xv[q] = __builtin_fmaf(alpha, pv[q], xv[q]);
+      const float rn = __builtin_fmaf(-alpha, qv[q], rv[q]);
+      rv[q] = BT * q < rows ? rn : 0.0f;
     }
-    rr_prev = rr;
-    if (!cg_product<W>(s, c, tag, words.rr, a, sh, rr)) return CG_ABORTED;
+    // the first and the last wave hold the chunk's first and last HALO rows
+    if (nch > 1 && t < HALO)
+      st_dev(&words.halo[c * (2 * HALO) + t], ((uint64_t)tag << 32) | (uint32_t)f2i(rv[0]));
+    if (nch > 1 && t >= BT - HALO)
+      st_dev(&words.halo[c * (2 * HALO) + HALO + lane], ((uint64_t)tag << 32) | (uint32_t)f2i(rv[R - 1]));
+#pragma unroll
+    for (int q = 0; q < R; q++) s = s + (double)rv[q] * (double)rv[q];
+    const double rr_prev = rr;
+    const auto next_halo = [&] {
+      uint32_t bits = 0u;
+      if (halo && !cg_poll(hword, tag, a, bits)) sh.ok = 0u;
+      hr = i2f((int)bits);
+    };
+    if (!cg_product<W>(s, tag, words.rr + my, words.rr + copy, nch, copies, a, sh, rr, next_halo)) return CG_ABORTED;
+    beta = (float)(rr / rr_prev);
   }
 }
 
