@@ -339,8 +339,8 @@ __global__ __launch_bounds__(1024) void k_lookback(const int32_t *__restrict__ x
 // b, chunks are small enough to spread over the chip, and every block reads
 // the aggregates of all chunks before it at once: one exchange instead of a
 // chain.  Time per call in a graph of calls (empty kernel 2.5 us): scan of
-// 1000 / 65,613 / 1,000,003 / 4,194,304 elements 3.2 / 4.4 / 5.9 / 8.0 us, with
-// k_lookback 5.6 / 6.9 / 12.8 / 12.6 us; compaction 3.4 / 4.8 / 6.3 / 8.8
+// 1000 / 65,613 / 1,000,003 / 4,194,304 elements 3.2 / 4.4 / 4.8 / 6.4 us, with
+// k_lookback 5.6 / 6.9 / 12.8 / 12.6 us; compaction 3.4 / 4.8 / 5.1 / 6.5
 // us, 7.2 / 8.6 / 11.0 / 13.9.
 //
 // No ticket orders the blocks, so a block may wait for one that the device
@@ -360,6 +360,18 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
   // lane 31's value into lanes 32 .. 63 (rows 2 and 3)
   v += (uint32_t)dpp<0x143, 0xc>(0, (int)v);  // row_bcast:31
   return v;
+}
+
+// Ahead of the first reading of the aggregates: one that comes too early has
+// to be repeated, a round trip later, and all blocks' early readings are in
+// the way of the aggregates' stores.  By the number of chunks (units of 64
+// cycles; us per scan / compaction without and with the wait): up to 16 none
+// (20,000 elements 4.8 / 4.6, 4.9 / 4.7 with 12), then 14 (1,000,003: 6.0 / 6.3
+// and 4.8 / 5.1; 2^22: 8.3 / 8.7 and 6.4 / 6.5), past 512 chunks 28 (2^23: scan
+// 17.3 and 13.1; 2^24: compaction 26.7 and 24.3).
+__device__ __forceinline__ void once_wait(int nch) {
+  if (nch > 512) __builtin_amdgcn_s_sleep(28);
+  else if (nch > 16) __builtin_amdgcn_s_sleep(14);
 }
 
 template <int K, int BT, int MODE>
@@ -451,6 +463,7 @@ __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *
   if (nch > 1) {
     const uint32_t tag = tag_of_epoch(s_epoch);
     if (t == 0) st_dev(&status[c], st_pack(tag, ST_AGG, agg));
+    once_wait(nch);
     // thread t: the aggregates of chunks t, t + BT, .. below c
     constexpr int NP = (ONCE_CHUNKS + BT - 1) / BT;
     uint64_t w[NP];
@@ -559,11 +572,11 @@ using once_fn = void (*)(const int32_t *, int32_t *, long long *, int64_t, int, 
 // The kernel for n elements, by measurement (us per call, scan / compaction):
 //  - up to 2^18 elements 8192 a block with 1024 threads, 8 a lane: fewest
 //    blocks to read from (131,072: 4.5 / 4.9; 1024-element chunks 5.5 / 5.7);
-//  - then 8192 with 512 threads, 16 a lane (1,000,003: 6.0 / 6.5, 4096-element
-//    chunks 6.4 / 6.5; 2^22: 8.4 / 8.7, 16384-element chunks 11.4 / 8.9), for
-//    compaction up to 2^22, for scans up to 2^23 (17.2; k_lookback 19.3);
-//  - compaction goes on with 16384 a block up to 2^24 (2^23: 12.7, with 8192
-//    15.4, k_lookback 17.9; 2^24: 26.7, k_lookback 28.0).
+//  - then up to 2^23 8192 with 512 threads, 16 a lane (3 x 2^20: 5.6 / 6.3,
+//    16384 a block 9.5 / 6.4; 6 x 2^20: 8.1 / 8.4 and 14.4 / 10.4, k_lookback
+//    16 / 16; 2^23: 13.1 / 11.2 and 16.4 / 11.2, k_lookback 19.3 / 17.9);
+//  - compaction goes on with 16384 a block up to 2^24 (24.0, k_lookback 28.0;
+//    a scan of 2^24 would take 31.9, with k_lookback 30).
 // Past that the aggregates that every block reads (the square of the blocks)
 // cost more than the tickets and windows of k_lookback.
 struct OncePick {
@@ -573,7 +586,7 @@ struct OncePick {
 template <int MODE>
 static OncePick pick_once(int64_t n) {
   if (n <= 1 << 18) return {k_once<8, 1024, MODE>, 8192, 1024};
-  if (n <= (MODE == MODE_SCAN ? 1 << 23 : 1 << 22)) return {k_once<16, 512, MODE>, 8192, 512};
+  if (n <= 1 << 23) return {k_once<16, 512, MODE>, 8192, 512};
   if constexpr (MODE == MODE_COMPACT)
     if (n <= 1 << 24) return {k_once<16, 1024, MODE>, 16384, 1024};
   return {nullptr, 0, 0};
