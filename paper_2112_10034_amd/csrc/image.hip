@@ -10,7 +10,8 @@
 //                (colsum[b][x]), row sums (rowsum[s][y]) and the tile total
 //                (total[b][s]);
 //   k_ii_colscan per column: colsum[b][x] replaced by its exclusive prefix
-//                over the bands above, T[b][x] (8 waves per 64 columns);
+//                over the bands above, T[b][x] (8 waves per 64 columns; with
+//                few bands k_ii_scan sums them itself instead);
 //   k_ii_scan    per tile: sat[y][x] = rowprefix_x(T[b][.] + column sums
 //                of rows y0..y)[x] + corner + sum of L over rows y0..y,
 //                with L[y] the row sums of the segments to the left and
@@ -59,6 +60,8 @@ struct IiArgs {
   uint32_t *colsum;   // [nb][W]: column sums, then their exclusive prefix T
   uint32_t *rowsum;   // [ns][H]
   uint32_t *total;    // [nb][ns]
+  bool whole;         // k_ii_scan: one segment, all rows above are summed from the image
+  bool direct;        // k_ii_scan: colsum holds the bands' sums, not yet their prefix
 };
 
 // Tile number of work item i: the tiles are handed out so that each XCD
@@ -364,8 +367,8 @@ __device__ __forceinline__ uint32_t ii_wave_scan(uint32_t v) {
 
 // One step of the butterfly below: 2H values to H, lanes exchanging with
 // lane ^ M (the lane's bit of M says which half it keeps).
-template <int M, int H>
-__device__ __forceinline__ void ii_halve(uint32_t (&v)[64], int lane) {
+template <int M, int H, int N>
+__device__ __forceinline__ void ii_halve(uint32_t (&v)[N], int lane) {
   const bool up = (lane & M) != 0;
 #pragma unroll
   for (int i = 0; i < H; i++) {
@@ -376,71 +379,143 @@ __device__ __forceinline__ void ii_halve(uint32_t (&v)[64], int lane) {
 }
 
 // Tile scans.  Wave w of the block holds columns 256w .. 256w + 255 of the
-// tile (4 a lane) and all its 64 rows: every pixel is requested before
-// anything else, 64 words a lane, so no row waits for memory.  Of the other
-// waves it needs the sums of their column carries and their row sums, which a
-// butterfly leaves one row per lane, so the block meets at one barrier per
-// tile; the carry of row y (corner, segments and waves to the left, over the
-// rows up to y) is then a scan over the lanes, and row y takes it from lane y.
-// Bound by the table's stores.  Reading four rows at a time, with a barrier
-// and shared-memory warp totals for each four, the rounds' latency bound it:
-// the same 70 us whatever the order of the tiles; now 55 us for 8192 x 8192
-// pixels (see ii_tile), 4.9 TB/s of image and table.
-template <int MODE>
+// tile (4 a lane) and all its TH rows: every pixel is requested before
+// anything else, a word a row and lane, so no row waits for memory.  Of the
+// other waves it needs the sums of their column carries and their row sums,
+// which a butterfly leaves one row per lane, so the block meets at one barrier
+// per tile; the carry of row y (corner, segments and waves to the left, over
+// the rows up to y) is then a scan over the lanes, and row y takes it from
+// lane y.  Bound by the table's stores for large images.  Reading four rows at
+// a time, with a barrier and shared-memory warp totals for each four, the
+// rounds' latency bound it: the same 70 us whatever the order of the tiles; now
+// 55 us for 8192 x 8192 pixels (see ii_tile), 4.9 TB/s of image and table.
+//
+// TH = 64: the bands of the reduce kernel.  TH = 16 and 32: for images whose
+// 64-row tiles leave the chip idle, where the 64 rows' scans of one wave (some
+// 10 us) bound the call; the tile adds up the rows of its band above it (at
+// most 48, read again from the image) to its column carries.
+template <int MODE, int TH>
 __global__ __launch_bounds__(II_BT, 4) void k_ii_scan(IiArgs a) {
   static_assert(II_TH == 64 && II_TW == 4 * 256 && II_BT == 256, "a wave per 256 columns, a lane per row");
-  __shared__ uint32_t s_rt[4][II_TH], s_above[4];  // the waves' row sums, sums of their column carries
+  static_assert(TH == 64 || TH == 32 || TH == 16, "row sums of 64, 32 or 16 rows");
+  __shared__ uint32_t s_rt[4][TH], s_above[4];  // the waves' row sums, sums of their column carries
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  for (int64_t i = blockIdx.x; i < a.nb * a.ns; i += gridDim.x) {
-    const int64_t tile = ii_tile(i, a.nb * a.ns), b = tile / a.ns, s = tile % a.ns;
-    const int64_t y0 = b * II_TH, x = s * II_TW + 4 * t;
-    const int rows = (int)(a.H - y0 < II_TH ? a.H - y0 : II_TH), cols = ii_cols(a, x);
+  const int64_t tiles = (a.H + TH - 1) / TH * a.ns;
+  for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
+    const int64_t tile = ii_tile(i, tiles), bt = tile / a.ns, s = tile % a.ns;
+    const int64_t b = TH == II_TH ? bt : a.whole ? 0 : bt / (II_TH / TH);  // band
+    const int64_t y0 = bt * TH, x = s * II_TW + 4 * t;
+    const int rows = (int)(a.H - y0 < TH ? a.H - y0 : TH), cols = ii_cols(a, x);
+    const int over = (int)(y0 - b * II_TH);  // rows of the band above the tile, a multiple of TH
     // pixels of row r (column x + j in byte j); rows and lanes past the image
     // read a valid row or the row's start and are cleared below
-    uint32_t px[II_TH];
+    uint32_t px[TH];
     const uint8_t *src = a.img + y0 * a.W + (cols ? x : 0);
     const int load_cols = cols ? cols : (a.W < 4 ? (int)a.W : 4);
 #pragma unroll
-    for (int r = 0; r < II_TH; r++) px[r] = ii_word<MODE>(src + (r < rows ? r : rows - 1) * a.W, load_cols);
+    for (int r = 0; r < TH; r++) px[r] = ii_word<MODE>(src + (r < rows ? r : rows - 1) * a.W, load_cols);
     // column carries: the band sums above
-    uint32_t c[4];
+    uint32_t c[4] = {0u, 0u, 0u, 0u};
+    if (TH == II_TH || !a.direct) {
 #pragma unroll
-    for (int j = 0; j < 4; j++) c[j] = j < cols ? a.colsum[b * a.W + x + j] : 0u;
+      for (int j = 0; j < 4; j++) c[j] = j < cols ? a.colsum[b * a.W + x + j] : 0u;
+    } else if (cols) {
+      // lanes at the edge read, and drop, columns before their own
+      const uint32_t *cp = a.colsum + (cols == 4 || a.W < 4 ? x : a.W - 4);
+      for (int64_t k0 = 0; k0 < b; k0 += 8) {
+        ii_u32x4u v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+          const uint32_t *q = cp + (k0 + k < b ? k0 + k : 0) * a.W;
+          if constexpr (MODE == II_NARROW) v[k] = ii_u32x4u{q[0], cols > 1 ? q[1] : 0u, cols > 2 ? q[2] : 0u, 0u};
+          else v[k] = *(const ii_u32x4u *)q;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+#pragma unroll
+          for (int j = 0; j < 4; j++) c[j] += k0 + k < b ? v[k][j] : 0u;
+      }
+      if constexpr (MODE == II_ANY)
+        if (cols < 4) {
+          const int sh = 4 - cols;  // column x is element sh of the vector
+          c[0] = sh == 1 ? c[1] : sh == 2 ? c[2] : c[3];
+          c[1] = sh == 1 ? c[2] : sh == 2 ? c[3] : 0u;
+          c[2] = sh == 1 ? c[3] : 0u;
+          c[3] = 0u;
+        }
+    }
+    if constexpr (TH < II_TH) {
+      // packed two to a word (at most 64 * 255 each)
+      const uint8_t *up = src - over * a.W;
+      for (int r0 = 0; r0 < over; r0 += 64) {
+        uint32_t ev = 0u, od = 0u;
+        for (int r1 = r0; r1 < r0 + 64 && r1 < over; r1 += TH) {
+          uint32_t q[TH];
+#pragma unroll
+          for (int r = 0; r < TH; r++) q[r] = ii_word<MODE>(up + (r1 + r) * a.W, load_cols);
+#pragma unroll
+          for (int r = 0; r < TH; r++) {
+            ev += q[r] & 0x00ff00ffu;
+            od += (q[r] >> 8) & 0x00ff00ffu;
+          }
+        }
+        if (cols) {
+          c[0] += ev & 0xffffu;
+          c[1] += od & 0xffffu;
+          c[2] += ev >> 16;
+          c[3] += od >> 16;
+        }
+      }
+    }
     // lane r: row y0 + r's sums of the segments to the left, and the totals
     // of the tiles above and to the left
     uint32_t left = 0u, cv = 0u;
     for (int64_t k = 0; k < s; k++) {
       if (lane < rows) left += a.rowsum[k * a.H + y0 + lane];
+      if (TH < II_TH && lane < over) cv += a.rowsum[k * a.H + b * II_TH + lane];
       for (int64_t bb = lane; bb < b; bb += 64) cv += a.total[bb * a.ns + k];
     }
     uint32_t corner = (uint32_t)__builtin_amdgcn_readlane((int)ii_wave_scan(cv), 63);
     const uint32_t above = ii_wave_scan(c[0] + c[1] + c[2] + c[3]);
     if (lane == 63) s_above[w] = above;
 #pragma unroll
-    for (int r = 0; r < II_TH; r++)
+    for (int r = 0; r < TH; r++)
       if (r >= rows || cols == 0) px[r] = 0u;
-    uint32_t v[64];
+    uint32_t v[TH];
 #pragma unroll
-    for (int r = 0; r < 64; r++) v[r] = __builtin_amdgcn_sad_u8(px[r], 0u, 0u);
-    // lane r ends with row r's sum: the halves kept at each step are chosen
-    // by the row's bits from the highest down
-    ii_halve<32, 32>(v, lane);
-    ii_halve<16, 16>(v, lane);
-    ii_halve<8, 8>(v, lane);
-    ii_halve<4, 4>(v, lane);
-    ii_halve<2, 2>(v, lane);
-    ii_halve<1, 1>(v, lane);
-    s_rt[w][lane] = v[0];
+    for (int r = 0; r < TH; r++) v[r] = __builtin_amdgcn_sad_u8(px[r], 0u, 0u);
+    if constexpr (TH == 64) {
+      // lane r ends with row r's sum: the halves kept at each step are chosen
+      // by the row's bits from the highest down
+      ii_halve<32, 32>(v, lane);
+      ii_halve<16, 16>(v, lane);
+      ii_halve<8, 8>(v, lane);
+      ii_halve<4, 4>(v, lane);
+      ii_halve<2, 2>(v, lane);
+      ii_halve<1, 1>(v, lane);
+      s_rt[w][lane] = v[0];
+    } else if constexpr (TH == 32) {
+      ii_halve<32, 16>(v, lane);
+      ii_halve<16, 8>(v, lane);
+      ii_halve<8, 4>(v, lane);
+      ii_halve<4, 2>(v, lane);
+      ii_halve<2, 1>(v, lane);
+      v[0] += (uint32_t)xor_lane<1>((int)v[0]);
+      if ((lane & 1) == 0) s_rt[w][lane >> 1] = v[0];
+    } else {
+      const uint32_t rs = ii_wave_sum16(v);
+      if ((lane & 3) == 0) s_rt[w][lane >> 2] = rs;
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-      left += k < w ? s_rt[k][lane] : 0u;
+      left += k < w && lane < TH ? s_rt[k][lane & (TH - 1)] : 0u;
       corner += k < w ? s_above[k] : 0u;
     }
     left = corner + ii_wave_scan(left);
     uint32_t *dst = a.sat + y0 * a.W + x;
 #pragma unroll
-    for (int r = 0; r < II_TH; r++) {
+    for (int r = 0; r < TH; r++) {
 #pragma unroll
       for (int j = 0; j < 4; j++) c[j] += (px[r] >> (8 * j)) & 0xffu;
       uint32_t q[4];
@@ -512,14 +587,35 @@ extern "C" cox_status cox_integral_image(const uint8_t *img, int64_t height, int
   const bool vec16 = width % 16 == 0 && ((uintptr_t)img & 15u) == 0;
   auto reduce = vec16 ? k_ii_reduce16<II_VEC> : width >= 16 ? k_ii_reduce16<II_ANY>
                 : width >= 4 ? k_ii_reduce<II_ANY> : k_ii_reduce<II_NARROW>;
-  auto scan = vec ? k_ii_scan<II_VEC> : width >= 4 ? k_ii_scan<II_ANY> : k_ii_scan<II_NARROW>;
-  hipStream_t hs = (hipStream_t)stream;
   const int64_t tiles = a.nb * a.ns;
-  const int g1 = persistent_grid((const void *)reduce, II_BT, tiles, 0, 0, 8);
-  hipLaunchKernelGGL(reduce, dim3(g1), dim3(II_BT), 0, hs, a);
-  const int64_t gc = (width + 63) / 64;
-  hipLaunchKernelGGL(k_ii_colscan, dim3((unsigned)(gc < 65536 ? gc : 65536)), dim3(64 * II_CS_WAVES), 0, hs, a);
-  const int g3 = persistent_grid((const void *)scan, II_BT, tiles, 0, 0, 8);
+  // Rows per tile of the scan kernel, by the number of 64-row tiles: 64-row
+  // tiles leave the chip idle up to about 250 of them, 16-row tiles read the
+  // rows above them once too often from 64 on (us per call with 16 / 32 / 64:
+  // 1000 x 1000 pixels, 16 tiles, 14.2 / 15.7 / 19.0; 2048 x 2048, 64, 15.0 /
+  // 16.5 / 20.8; 2500 x 2500, 120, 22.7 / 20.9 / 23.8; 4000 x 4000, 252, 31.8 /
+  // 27.1 / 27.3; 6000 x 6000, 564, 67 / 58 / 52).
+  const int th = tiles <= 64 ? 16 : tiles <= 192 ? 32 : 64;
+  auto scan = th == 16 ? (vec ? k_ii_scan<II_VEC, 16> : width >= 4 ? k_ii_scan<II_ANY, 16> : k_ii_scan<II_NARROW, 16>)
+              : th == 32
+                  ? (vec ? k_ii_scan<II_VEC, 32> : width >= 4 ? k_ii_scan<II_ANY, 32> : k_ii_scan<II_NARROW, 32>)
+                  : (vec ? k_ii_scan<II_VEC, 64> : width >= 4 ? k_ii_scan<II_ANY, 64> : k_ii_scan<II_NARROW, 64>);
+  // One segment and up to 256 rows: the scan kernel alone, adding up the rows
+  // above a tile from the image (64 / 256 / 512 rows: 6.1 / 9.5 / 13.9 us, with
+  // the reduce kernel 9.6 / 10.5 / 10.8).
+  a.whole = th == 16 && a.ns == 1 && height <= 256;
+  // Up to 40 bands the scan kernel adds up the bands' column sums itself, and
+  // the column kernel's launch is saved (1000 x 1000: 14.2 and 12.0 us; 2048 x
+  // 2048 16.1 and 14.9; 47 bands 16.2 and 16.0, 94 bands 14.4 and 16.8).
+  a.direct = th < 64 && a.nb <= 40;
+  hipStream_t hs = (hipStream_t)stream;
+  if (!a.whole) {
+    const int g1 = persistent_grid((const void *)reduce, II_BT, tiles, 0, 0, 8);
+    hipLaunchKernelGGL(reduce, dim3(g1), dim3(II_BT), 0, hs, a);
+    const int64_t gc = (width + 63) / 64;
+    if (!a.direct)
+      hipLaunchKernelGGL(k_ii_colscan, dim3((unsigned)(gc < 65536 ? gc : 65536)), dim3(64 * II_CS_WAVES), 0, hs, a);
+  }
+  const int g3 = persistent_grid((const void *)scan, II_BT, (height + th - 1) / th * a.ns, 0, 0, 8);
   hipLaunchKernelGGL(scan, dim3(g3), dim3(II_BT), 0, hs, a);
   return launch_status();
 }
