@@ -1,9 +1,9 @@
 // Warp-shuffle reductions.
 //
-// k_reduce_blocks_i32: 256-thread blocks of 8 logical warps, one element
-// per thread; shfl_down tree per warp, ballot(x > 0) per warp, shared-memory
-// combine of the 8 warp values by warp 0 (the SDK reduction pattern that
-// COX's Code 1 simplifies, Sec. 2.3).
+// k_reduce_blocks_i32: sums of 256 elements and positive counts of 32, what the
+// SDK reduction pattern that COX's Code 1 simplifies (Sec. 2.3) gives with
+// 256-thread blocks of 8 logical warps: shfl_down tree and ballot(x > 0) per
+// warp, shared-memory combine of the 8 warp values by warp 0.
 //
 // k_reduce: chunked sum / dot under the fixed schedule sigma = (k, W)
 // (documented in cox.h); persistent blocks walk chunks c = b, b + G, ...;
@@ -26,35 +26,68 @@
 namespace cox {
 
 // ---------------------------------------------------------------- K-R0
-__device__ __forceinline__ uint32_t tree_u32(uint32_t v) {
-  v += (uint32_t)xor_lane<16>((int)v);
-  v += (uint32_t)xor_lane<8>((int)v);
-  v += (uint32_t)xor_lane<4>((int)v);
-  v += (uint32_t)xor_lane<2>((int)v);
-  v += (uint32_t)xor_lane<1>((int)v);
-  return v;
-}
-
+// A wave takes R = 2 consecutive groups of 256 elements (a reduction block
+// each), a 16-byte load per group and lane, requested together: no shared
+// memory, no barrier.  Positive counts of the 8 lanes of a logical warp's 32
+// elements are bytes of one word; a group's sum is a DPP scan's last lane.  The
+// sums are mod 2^32, so any order gives the same.  Bound by the reads: us per
+// call at 2^20 / 2^22 / 2^24 / 2^26 elements 3.3 / 5.3 / 13.0 / 44.4 (6.1 TB/s
+// at 2^26); with an element per thread, trees through ds_swizzle and a barrier
+// 4.3 / 9.9 / 30.1 / 152.  R = 1 / 4 / 8: 53.8 / 45.8 / 45.7 at 2^26.
+constexpr int RB_R = 2;
+template <bool STREAM>
 __global__ __launch_bounds__(256) void k_reduce_blocks_i32(const int32_t *__restrict__ x, int64_t n,
                                                            int32_t *__restrict__ bsum,
                                                            int32_t *__restrict__ wpos) {
-  __shared__ uint32_t slot[8];
-  const int t = threadIdx.x, w = t >> 5, l = t & 31;
-  const int64_t e = (int64_t)blockIdx.x * 256 + t;
-  const int32_t xv = e < n ? x[e] : 0;
-  uint32_t v = tree_u32((uint32_t)xv);
-  const uint32_t b = ballot(xv > 0);
-  if (l == 0) {
-    const int64_t g = (int64_t)blockIdx.x * 8 + w;
-    if (32 * g < n) wpos[g] = __popc(b);
-    slot[w] = v;
+  constexpr int R = RB_R;
+  static_assert(R <= 4, "an octet's lanes each store one group's count, a byte of one word");
+  typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // x of any alignment
+  const int lane = threadIdx.x & 63;
+  const int64_t g0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
+  if (256 * g0 >= n) return;
+  const int64_t e = 256 * g0 + 4 * lane;
+  u32x4a4 q[R];
+  if (256 * (g0 + R) <= n) {
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      const u32x4a4 *p = (const u32x4a4 *)(x + e + 256 * r);
+      if constexpr (STREAM) q[r] = __builtin_nontemporal_load(p);
+      else q[r] = *p;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; r++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int64_t i = e + 256 * r + j;
+        const uint32_t v = (uint32_t)x[i < n ? i : n - 1];
+        q[r][j] = i < n ? v : 0u;
+      }
   }
-  __syncthreads();
-  if (w == 0) {
-    uint32_t a = l < 8 ? slot[l] : 0u;
-    a = tree_u32(a);
-    if (l == 0) bsum[blockIdx.x] = (int32_t)a;
+  uint32_t cnt = 0u, out = 0u;
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    uint32_t c = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; j++) c += (int32_t)q[r][j] > 0 ? 1u : 0u;
+    cnt += c << (8 * r);
+    uint32_t v = (q[r][0] + q[r][1]) + (q[r][2] + q[r][3]);
+    v += (uint32_t)dpp<DPP_ROW_SHR1>(0, (int)v);
+    v += (uint32_t)dpp<DPP_ROW_SHR2>(0, (int)v);
+    v += (uint32_t)dpp<DPP_ROW_SHR4>(0, (int)v);
+    v += (uint32_t)dpp<DPP_ROW_SHR8>(0, (int)v);
+    v += (uint32_t)dpp<DPP_ROW_BCAST15, 0xa>(0, (int)v);
+    v += (uint32_t)dpp<0x143, 0xc>(0, (int)v);  // row_bcast:31
+    const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    out = lane == r ? sum : out;
   }
+  cnt += (uint32_t)xor_lane<1>((int)cnt);
+  cnt += (uint32_t)xor_lane<2>((int)cnt);
+  cnt += (uint32_t)xor_lane<7>((int)cnt);  // the other quad of the octet
+  const int r = lane & 7;                  // lane r of an octet stores group r's count
+  const int64_t g = 8 * (g0 + r) + (lane >> 3);
+  if (r < R && 32 * g < n) wpos[g] = (int32_t)((cnt >> (8 * (r & 3))) & 0xffu);
+  if (lane < R && 256 * (g0 + lane) < n) bsum[g0 + lane] = (int32_t)out;
 }
 
 // ---------------------------------------------------------------- chunked reduce
@@ -588,7 +621,11 @@ cox_status cox_warp_reduce_blocks_i32(const int32_t *x, int64_t n, int32_t *bloc
   if (!x || !block_sums || !warp_pos_count) return COX_ERR_INVALID;
   const int64_t nb = (n + 255) / 256;
   if (nb > 0x7fffffff) return COX_ERR_INVALID;
-  hipLaunchKernelGGL(k_reduce_blocks_i32, dim3((unsigned)nb), dim3(256), 0, (hipStream_t)stream, x, n,
+  // Inputs that the L2 caches can hold are read with ordinary loads (2^20: 3.3
+  // us, with streaming ones 3.8; 2^21 3.4 and 4.3), larger ones with streaming
+  // loads (2^22: 5.6 and 5.3; 2^26 47.6 and 44.4).
+  auto fn = n <= 1 << 21 ? k_reduce_blocks_i32<false> : k_reduce_blocks_i32<true>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)((nb + 4 * RB_R - 1) / (4 * RB_R))), dim3(256), 0, (hipStream_t)stream, x, n,
                      block_sums, warp_pos_count);
   return launch_status();
 }
