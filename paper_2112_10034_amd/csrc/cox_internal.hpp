@@ -10,7 +10,7 @@ namespace cox {
 
 // ---------------------------------------------------------------- workspace
 // First 256 bytes: header words; data (status words / partials) follows.
-enum : int { HDR_TICKET = 0, HDR_EPOCH = 1, HDR_DONE = 2, HDR_ERR = 3, HDR_GROUP0 = 8, HDR_WORDS = 64 };
+enum : int { HDR_TICKET = 0, HDR_EPOCH = 1, HDR_ERR = 3, HDR_WORDS = 64 };
 constexpr size_t WS_HEADER = 256;
 
 // HDR_ERR holds the tag of a call whose bounded wait gave up; ERR_LAYOUT

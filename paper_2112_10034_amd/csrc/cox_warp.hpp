@@ -160,4 +160,40 @@ __device__ __forceinline__ double xor_lane_d(double v) {
   return __builtin_bit_cast(double, p);
 }
 
+// The steps at offsets 16 and 4 of a shfl_down tree (16, 8, 4, 2, 1) by VALU
+// moves instead of ds_swizzle, whose way through the shared-memory crossbar
+// costs some 100 cycles each.  For a commutative combine every lane of the
+// warp ends with the tree's value; lane 0's operands are its own and lane
+// o's, in that order, as shfl_down's are.
+// Step 16: v_permlane16_swap of v with itself gives both rows the value of
+// row 0 (own) and of row 1 (partner).
+__device__ __forceinline__ void tree16(uint32_t v, uint32_t &own, uint32_t &partner) {
+  const auto pr = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  own = pr[0];
+  partner = pr[1];
+}
+// Step 4, after step 8: lane l takes lane l + 4 of its row (cyclic); lanes l
+// and l + 8 are equal by then.
+__device__ __forceinline__ int tree4(int v) { return dpp_mov<0x12c>(v); }  // row_ror:12
+__device__ __forceinline__ double tree4_d(double v) {
+  int2 p = __builtin_bit_cast(int2, v);
+  p.x = tree4(p.x);
+  p.y = tree4(p.y);
+  return __builtin_bit_cast(double, p);
+}
+
+// FP64 sum over a logical warp in the order of the shfl_down tree, in every lane
+__device__ __forceinline__ double tree_f64(double v) {
+  const uint2 p = __builtin_bit_cast(uint2, v);
+  uint2 a, b;
+  tree16(p.x, a.x, b.x);
+  tree16(p.y, a.y, b.y);
+  v = __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+  v = v + xor_lane_d<8>(v);
+  v = v + tree4_d(v);
+  v = v + xor_lane_d<2>(v);
+  v = v + xor_lane_d<1>(v);
+  return v;
+}
+
 }  // namespace cox

@@ -190,42 +190,17 @@ struct CgShared {
   float win[32 * W * R + 2 * HALO + 1];  // and a zero (cg_near)
 };
 
-// xor butterfly over a logical warp: every lane ends with the value lane 0
-// of the shfl_down tree (offsets 16 .. 1) holds
-//
-// All five steps are VALU moves, none a ds_swizzle: offset 16 by
-// v_permlane16_swap of v with itself (each row's value beside its
-// partner's, in one order or the other), offset 4 by a rotation, since
-// lanes l and l + 8 of a row are equal by then.
-__device__ __forceinline__ double ror4_d(double v) {
-  int2 p = __builtin_bit_cast(int2, v);
-  p.x = dpp_mov<0x124>(p.x);
-  p.y = dpp_mov<0x124>(p.y);
-  return __builtin_bit_cast(double, p);
-}
-__device__ __forceinline__ double tree64(double v) {
-  const uint2 p = __builtin_bit_cast(uint2, v);
-  const auto x = __builtin_amdgcn_permlane16_swap(p.x, p.x, false, false);
-  const auto y = __builtin_amdgcn_permlane16_swap(p.y, p.y, false, false);
-  v = __hiloint2double((int)y[0], (int)x[0]) + __hiloint2double((int)y[1], (int)x[1]);
-  v = v + xor_lane_d<8>(v);
-  v = v + ror4_d(v);
-  v = v + xor_lane_d<2>(v);
-  v = v + xor_lane_d<1>(v);
-  return v;
-}
-
 // chunk value of a per-thread FP64 sum: warp trees, then warp 0's tree over
 // the W warp values (-0.0 beyond W); thread 0 stores it.  Ends with a block
 // barrier, so the shared window may be reused after it.
 template <int W, class SH>
 __device__ __forceinline__ void chunk_store(double s, double *part, int64_t c, SH &sh) {
   const int t = threadIdx.x, l = t & 31;
-  s = tree64(s);
+  s = tree_f64(s);
   if (l == 0) sh.slot[t >> 5] = s;
   __syncthreads();
   if (t < 32) {
-    const double v = tree64(l < W ? sh.slot[l] : -0.0);
+    const double v = tree_f64(l < W ? sh.slot[l] : -0.0);
     if (t == 0) stcd(&part[c], v);
   }
   __syncthreads();
@@ -255,10 +230,10 @@ __device__ __forceinline__ double final64(const double *part, int64_t nch, SH &s
     double top = -0.0;
 #pragma unroll
     for (int vw = 0; vw < 8; vw++) {
-      const double v = tree64(sh.fin[32 * vw + l]);
+      const double v = tree_f64(sh.fin[32 * vw + l]);
       if (l == vw) top = v;
     }
-    top = tree64(top);
+    top = tree_f64(top);
     if (t == 0) sh.bcast = top;
   }
   __syncthreads();
@@ -729,11 +704,11 @@ __device__ __forceinline__ bool cg_product(double s, uint32_t tag, uint64_t *min
   constexpr int NW = W / 2;  // waves
   const int t = threadIdx.x, l = t & 31, lane = t & 63, wave = t >> 6;
   const int ng = (nch + 31) >> 5;
-  s = tree64(s);
+  s = tree_f64(s);
   if (l == 0) sh.slot[t >> 5] = s;
   __syncthreads();
   if (wave == NW - 2) {
-    const double v = tree64(l < W ? sh.slot[l] : -0.0);
+    const double v = tree_f64(l < W ? sh.slot[l] : -0.0);
     const uint64_t word = (uint64_t)tag << 32 | ((t & 1) ? (uint32_t)__double2loint(v) : (uint32_t)__double2hiint(v));
     if (nch == 1) {
       if (lane == 0) sh.fin[0] = v;
@@ -760,7 +735,7 @@ __device__ __forceinline__ bool cg_product(double s, uint32_t tag, uint64_t *min
       uint32_t bits = 0u;
       bool ok = true;
       if (lane < 2 * m) ok = cg_poll(theirs + 64 * g + lane, tag, a, bits);
-      const double v = tree64(cg_pair(bits, l, m));
+      const double v = tree_f64(cg_pair(bits, l, m));
       if (lane == 0) sh.fin[g] = v;
       if (!ok) sh.ok = 0u;
     }
@@ -770,7 +745,7 @@ __device__ __forceinline__ bool cg_product(double s, uint32_t tag, uint64_t *min
   // add the -0.0 of lanes 8 to 31)
   double v = (l & 7) < ng ? sh.fin[l & 7] : -0.0;
   const bool ok = sh.ok != 0u;
-  v = v + ror4_d(v);
+  v = v + tree4_d(v);
   v = v + xor_lane_d<2>(v);
   v = v + xor_lane_d<1>(v);
   out = v;

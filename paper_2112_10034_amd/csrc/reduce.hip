@@ -8,19 +8,24 @@
 // k_reduce: chunked sum / dot under the fixed schedule sigma = (k, W)
 // (documented in cox.h); persistent blocks walk chunks c = b, b + G, ...;
 // every chunk partial is published as a 64-bit word [tag | value bits]
-// with a device-scope atomic store (tag = this call's epoch), and the last
-// block to finish (device-scope counter) collects the words, checking each
-// tag, and runs the FP64 (or int64) final combine.  A single chunk's value is
-// the total at once.  No memory fences are
-// needed: a word with the current tag can only hold this call's partial,
-// and the last block resets the counter and advances the epoch only after
-// it has seen every block's words, whose tags every block derived from its
-// own read of the epoch.
+// with a device-scope atomic store (tag = this call's epoch), and the grid's
+// last block, once it has published its own, collects the words, waiting for
+// each one's tag, and runs the FP64 (or int64) final combine.  A single
+// chunk's value is the total at once.  No memory fences are needed: a word
+// with the current tag can only hold this call's partial, and the last block
+// advances the epoch only after it has seen every block's words, whose tags
+// every block derived from its own read of the epoch.  Nobody but that one
+// block waits, so all others end whatever order they run in.  (With a counter
+// of finished blocks, the last of which combines, one or two more round trips
+// lay between: sums of 2^20 / 2^24 / 2^28 float32 8.4 / 17.6 / 162.7 us, 6.3 /
+// 16.0 / 161.2 now; dot of 2^28 330.6 and 320.)
 //
 // The shfl_down tree is evaluated at lane 0, which only ever reads
 // in-range sources (offset o reads lanes below 2o); the exchanges use the
 // xor partner l ^ o, which for every lane l < o is exactly l + o, so lane
 // 0's value is the one CUDA's __shfl_down_sync tree produces, bit for bit.
+#include <type_traits>
+
 #include "cox_internal.hpp"
 
 namespace cox {
@@ -192,35 +197,56 @@ __device__ __forceinline__ Acc acc_combine(Acc a, Acc b) {
   return a;
 }
 
-template <int M, int DT, int ACC>
-__device__ __forceinline__ Acc acc_xor(Acc a) {
-  Acc r = a;
+// a with every 32-bit value in use replaced by f of it
+template <int DT, int ACC, class F>
+__device__ __forceinline__ Acc acc_map(Acc a, F f) {
   if constexpr (DT == DT_I32) {
-    r.i = (uint32_t)xor_lane<M>((int)a.i);
+    a.i = (uint32_t)f((int)a.i);
   } else {
-    r.s = xor_lane_f<M>(a.s);
-    if constexpr (ACC == COX_ACC_TWOSUM) r.c = xor_lane_f<M>(a.c);
+    a.s = i2f(f(f2i(a.s)));
+    if constexpr (ACC == COX_ACC_TWOSUM) a.c = i2f(f(f2i(a.c)));
   }
-  return r;
+  return a;
 }
 
 // shfl_down tree, offsets 16, 8, 4, 2, 1 (value valid at lane 0)
 template <int DT, int ACC>
 __device__ __forceinline__ Acc warp_tree(Acc a) {
-  a = acc_combine<DT, ACC>(a, acc_xor<16, DT, ACC>(a));
-  a = acc_combine<DT, ACC>(a, acc_xor<8, DT, ACC>(a));
-  a = acc_combine<DT, ACC>(a, acc_xor<4, DT, ACC>(a));
-  a = acc_combine<DT, ACC>(a, acc_xor<2, DT, ACC>(a));
-  a = acc_combine<DT, ACC>(a, acc_xor<1, DT, ACC>(a));
+  const Acc b = acc_map<DT, ACC>(a, [](int v) {
+    uint32_t own, partner;
+    tree16((uint32_t)v, own, partner);
+    return (int)partner;
+  });
+  a = acc_map<DT, ACC>(a, [](int v) {
+    uint32_t own, partner;
+    tree16((uint32_t)v, own, partner);
+    return (int)own;
+  });
+  a = acc_combine<DT, ACC>(a, b);
+  a = acc_combine<DT, ACC>(a, acc_map<DT, ACC>(a, [](int v) { return xor_lane<8>(v); }));
+  a = acc_combine<DT, ACC>(a, acc_map<DT, ACC>(a, [](int v) { return tree4(v); }));
+  a = acc_combine<DT, ACC>(a, acc_map<DT, ACC>(a, [](int v) { return xor_lane<2>(v); }));
+  a = acc_combine<DT, ACC>(a, acc_map<DT, ACC>(a, [](int v) { return xor_lane<1>(v); }));
   return a;
 }
 
-__device__ __forceinline__ double tree_f64(double v) {
-  v = v + xor_lane_d<16>(v);
-  v = v + xor_lane_d<8>(v);
-  v = v + xor_lane_d<4>(v);
-  v = v + xor_lane_d<2>(v);
-  v = v + xor_lane_d<1>(v);
+// int64 sum over a logical warp, in every lane
+__device__ __forceinline__ long long tree_i64(long long v) {
+  auto moved = [&](auto f) {
+    uint2 p = __builtin_bit_cast(uint2, v);
+    p.x = (uint32_t)f((int)p.x);
+    p.y = (uint32_t)f((int)p.y);
+    return __builtin_bit_cast(long long, p);
+  };
+  const uint2 p = __builtin_bit_cast(uint2, v);
+  uint2 a, b;
+  tree16(p.x, a.x, b.x);
+  tree16(p.y, a.y, b.y);
+  v = __builtin_bit_cast(long long, a) + __builtin_bit_cast(long long, b);
+  v += moved([](int u) { return xor_lane<8>(u); });
+  v += moved([](int u) { return tree4(u); });
+  v += moved([](int u) { return xor_lane<2>(u); });
+  v += moved([](int u) { return xor_lane<1>(u); });
   return v;
 }
 
@@ -243,7 +269,8 @@ __device__ __forceinline__ void store_partial(void *part, uint64_t *pw, uint32_t
 }
 
 // a tagged word that did not yet carry `tag` when first read: wait for it
-// (bounded; running out sets HDR_ERR)
+// (bounded, by more than a second: the block that publishes it may still wait
+// behind another stream's kernel; running out sets HDR_ERR)
 __device__ __noinline__ uint64_t wait_word(const uint64_t *p, uint32_t tag, uint32_t *hdr) {
   uint64_t s = ld_dev(p);
   uint32_t spins = 0;
@@ -252,7 +279,8 @@ __device__ __noinline__ uint64_t wait_word(const uint64_t *p, uint32_t tag, uint
       st_dev32(&hdr[HDR_ERR], tag);
       break;
     }
-    __builtin_amdgcn_s_sleep(1);
+    if (spins < 256) __builtin_amdgcn_s_sleep(1);
+    else __builtin_amdgcn_s_sleep(32);
     s = ld_dev(p);
   }
   return s;
@@ -278,21 +306,6 @@ __device__ __forceinline__ void take_words(const uint64_t *p, int64_t i0, int64_
   }
 }
 
-// Counts this block as done; true for the last one of the grid.  Atomics on
-// one 64-byte unit take 11.5 ns each, one after another, and all blocks of a
-// full grid arrive at about the same time (256: 3 us), so larger grids count
-// in four groups, each on a unit of its own in the header, and then the
-// groups.  (One round trip more, 0.45 us, so small grids count directly.)
-__device__ __forceinline__ bool count_done(uint32_t *hdr) {
-  const uint32_t G = gridDim.x;
-  if (G <= 64) return add_dev32(&hdr[HDR_DONE], 1u) == G - 1;
-  const uint32_t g = blockIdx.x & 3u, members = (G - g + 3u) >> 2;
-  uint32_t *const word = &hdr[g ? 16u * g : (uint32_t)HDR_GROUP0];
-  if (add_dev32(word, 1u) != members - 1) return false;
-  st_dev32(word, 0u);
-  return add_dev32(&hdr[HDR_DONE], 1u) == 3u;
-}
-
 // Full chunks c = first + i * gridDim.x run double-buffered: the next
 // chunk's vectors are requested before the current chunk is reduced, so loads
 // stay in flight across the block's barrier.  A buffer holds the vectors as
@@ -315,7 +328,7 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   constexpr uint32_t XPAD = DT == DT_I32 ? 0u : DT == DT_BF16 ? 0x80008000u : 0x80000000u;
   __shared__ Acc slot[2][32];
   __shared__ double fin[256];
-  __shared__ uint32_t s_last, s_epoch;
+  __shared__ uint32_t s_epoch;
 
   const int W = blockDim.x >> 5;
   uint64_t *pw = (uint64_t *)(hdr + HDR_WORDS);
@@ -458,13 +471,10 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   }
   if (single) return;
 
-  // the last block to finish combines the chunk partials
-  if (threadIdx.x == 0) {
-    s_epoch = epoch;
-    s_last = count_done(hdr) ? 1u : 0u;
-  }
+  // the grid's last block combines the chunk partials
+  if (blockIdx.x != gridDim.x - 1) return;
+  if (threadIdx.x == 0) s_epoch = epoch;
   __syncthreads();
-  if (!s_last) return;
   epoch = s_epoch;
   const uint32_t tag = tag_of_epoch(epoch);
 
@@ -475,22 +485,26 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   if constexpr (DT == DT_I32) {
     __shared__ long long isum[32];
     long long s = 0;
-    for (int64_t c0 = threadIdx.x; c0 < nch; c0 += (int64_t)FB * blockDim.x) {
-      uint32_t buf[FB];
-      take_words<FB>(pw, c0, blockDim.x, nch, tag, hdr, 0u, buf);
+    auto batch = [&](auto fb, int64_t c0) {
+      constexpr int B = decltype(fb)::value;
+      uint32_t buf[B];
+      take_words<B>(pw, c0, blockDim.x, nch, tag, hdr, 0u, buf);
 #pragma unroll
-      for (int b = 0; b < FB; b++) s += (long long)(int32_t)buf[b];
-    }
+      for (int b = 0; b < B; b++) s += (long long)(int32_t)buf[b];
+    };
+    if (nch <= blockDim.x) batch(std::integral_constant<int, 1>{}, threadIdx.x);
+    else
+      for (int64_t c0 = threadIdx.x; c0 < nch; c0 += (int64_t)FB * blockDim.x)
+        batch(std::integral_constant<int, FB>{}, c0);
     // block sum of int64 (order does not matter for integers)
-    for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
+    s = tree_i64(s);
     if (l == 0) isum[w] = s;
     __syncthreads();
     if (threadIdx.x < 32) {
       long long tot = l < W ? isum[l] : 0;
-      for (int o = 16; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 32);
+      tot = tree_i64(tot);
       if (l == 0) {
         *(long long *)total = tot;
-        st_dev32(&hdr[HDR_DONE], 0u);
         st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
       }
     }
@@ -499,24 +513,28 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
     // padded with -0.0 at its end is unchanged
     for (int j = threadIdx.x; j < 256; j += blockDim.x) {
       double s = -0.0;
-      for (int64_t c0 = j; c0 < nch; c0 += (int64_t)FB * 256) {
-        double buf[FB];
+      auto batch = [&](auto fb, int64_t c0) {
+        constexpr int B = decltype(fb)::value;
+        double buf[B];
         if constexpr (ACC == COX_ACC_PLAIN) {
-          uint32_t v[FB];
-          take_words<FB>(pw, c0, 256, nch, tag, hdr, 0x80000000u, v);
+          uint32_t v[B];
+          take_words<B>(pw, c0, 256, nch, tag, hdr, 0x80000000u, v);
 #pragma unroll
-          for (int b = 0; b < FB; b++) buf[b] = (double)i2f((int)v[b]);
+          for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)v[b]);
         } else {
           // words 2c (s) and 2c + 1 (c); padding (-0.0, -0.0) adds -0.0
-          uint32_t vs[FB], vc[FB];
-          take_words<FB>(pw, 2 * c0, 512, 2 * nch, tag, hdr, 0x80000000u, vs);
-          take_words<FB>(pw, 2 * c0 + 1, 512, 2 * nch, tag, hdr, 0x80000000u, vc);
+          uint32_t vs[B], vc[B];
+          take_words<B>(pw, 2 * c0, 512, 2 * nch, tag, hdr, 0x80000000u, vs);
+          take_words<B>(pw, 2 * c0 + 1, 512, 2 * nch, tag, hdr, 0x80000000u, vc);
 #pragma unroll
-          for (int b = 0; b < FB; b++) buf[b] = (double)i2f((int)vs[b]) + (double)i2f((int)vc[b]);
+          for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)vs[b]) + (double)i2f((int)vc[b]);
         }
 #pragma unroll
-        for (int b = 0; b < FB; b++) s = s + buf[b];
-      }
+        for (int b = 0; b < B; b++) s = s + buf[b];
+      };
+      if (nch <= 256) batch(std::integral_constant<int, 1>{}, j);
+      else
+        for (int64_t c0 = j; c0 < nch; c0 += (int64_t)FB * 256) batch(std::integral_constant<int, FB>{}, c0);
       // the tree of each group of 32, by its own warp where there are eight
       if (blockDim.x >= 256) {
         s = tree_f64(s);
@@ -541,7 +559,6 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
       top = tree_f64(top);
       if (l == 0) {
         *(double *)total = top;
-        st_dev32(&hdr[HDR_DONE], 0u);
         st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
       }
     }
