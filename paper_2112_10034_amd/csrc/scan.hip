@@ -59,57 +59,69 @@ __device__ __forceinline__ uint32_t warp_sum_u32(uint32_t v) {
   return v;
 }
 
-// Decoupled look-back, run by the 32 lanes of logical warp 0, in two
-// halves so that other loads can be issued in between: lookback_begin
-// publishes the chunk's aggregate and requests the first window of
-// predecessor status words (lane l reads chunk c - 1 - l); lookback_end
-// waits for them, walks further back 32 chunks at a time until a lane
-// finds an inclusive prefix, and publishes the chunk's inclusive prefix.
-// Returns the exclusive prefix (same in every lane).
-__device__ __forceinline__ uint64_t lookback_begin(int64_t c, uint32_t agg, uint64_t *__restrict__ status,
-                                                   int64_t sst, uint32_t tag) {
-  const int l = llane();
-  if (c == 0) {
-    if (l == 0) st_dev(&status[0], st_pack(tag, ST_PREFIX, agg));
-    return 0;
-  }
-  if (l == 0) st_dev(&status[c * sst], st_pack(tag, ST_AGG, agg));
-  const int64_t idx = c - 1 - l;
+// Decoupled look-back, run by the lanes (64 or 32) of wave 0, in two halves so that
+// other loads can be issued in between: lookback_begin publishes the chunk's
+// aggregate and requests the status words of the 64 chunks before it (lane L
+// chunk c - 1 - L; 32 for small chunks); lookback_end waits for them as far as the nearest
+// inclusive prefix, walks further back if there is none, and publishes the
+// chunk's inclusive prefix.  Returns the exclusive prefix (same in every lane).
+//
+// The look-back is the longest part of a compaction's chunk (9900 of 20500
+// cycles at 2^28, and the next chunk's loads are back by half of it).  A request
+// that comes before the words is paid for with another round trip and stands
+// in the stores' way, so a wait comes first (units of 64 cycles; us at
+// 2^28 for 0 / 8 / 14 / 20 / 28 / 36 / 48: compaction 306 / 304 / 304 / 300 /
+// 295 / 291 / 292, scan 354 / 345 / 345 / 345 / 344 / 345 / 343).  64 words, 32
+// before: compaction 319 and 306, scan 353 and 355; 128 / 256 words 321 / 338 and
+// 368 / 388 without the wait.
+// Less than 64 chunks, all under way at once, are not waited for (2000 elements
+// 5.1 us, 5.6 with the wait); chunks below 16384 elements neither, and their
+// windows stay at 32 words (2^24 with 1024 / 4096 a chunk: scan 242 / 81.9,
+// with 64 words 254 / 84.3, and no wait gains it back).
+__device__ __forceinline__ int lb_lanes(int64_t S) { return S < 16384 ? 32 : 64; }
+
+__device__ __forceinline__ uint64_t lb_request(int64_t top, const uint64_t *__restrict__ status, int64_t sst,
+                                               uint32_t tag) {
+  const int64_t idx = top - (int)threadIdx.x;
   return idx >= 0 ? ld_dev(&status[idx * sst]) : st_pack(tag, ST_PREFIX, 0u);
 }
 
-__device__ uint32_t lookback_end(int64_t c, uint32_t agg, uint64_t first, uint64_t *__restrict__ status,
-                                 int64_t sst, uint32_t tag, uint32_t *__restrict__ hdr) {
-  const int l = llane();
+__device__ __forceinline__ uint64_t lookback_begin(int64_t c, uint32_t agg, int64_t nch, int64_t S,
+                                                   uint64_t *__restrict__ status, int64_t sst, uint32_t tag) {
+  if (threadIdx.x == 0) st_dev(&status[c * sst], st_pack(tag, c == 0 ? ST_PREFIX : ST_AGG, agg));
+  if (nch >= 64 && S >= 16384) __builtin_amdgcn_s_sleep(32);
+  return lb_request(c - 1, status, sst, tag);
+}
+
+__device__ __forceinline__ uint32_t lookback_end(int64_t c, uint32_t agg, uint64_t s, int lanes,
+                                                 uint64_t *__restrict__ status, int64_t sst, uint32_t tag,
+                                                 uint32_t *__restrict__ hdr) {
   if (c == 0) return 0u;
-  uint32_t run = 0u;
-  int64_t top = c - 1;
-  uint64_t s = first;
-  for (;;) {
-    const int64_t idx = top - l;
-    if (idx >= 0) {
-      uint32_t spins = 0;
-      while (st_tag(s) != tag || st_flag(s) == 0u) {
-        if (++spins >= MAX_SPIN || ((spins & 1023u) == 0u && ld_dev32(&hdr[HDR_ERR]) == tag)) {
-          st_dev32(&hdr[HDR_ERR], tag);  // give up: result invalid, kernel still ends
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        s = ld_dev(&status[idx * sst]);
-      }
+  const int L = (int)threadIdx.x;
+  uint32_t part = 0u, spins = 0u;  // this lane's words
+  for (int64_t top = c - 1;;) {
+    const bool ready = st_tag(s) == tag && st_flag(s) != 0u;
+    const uint64_t pm = __builtin_amdgcn_ballot_w64(ready && st_flag(s) == ST_PREFIX);
+    const uint64_t late = __builtin_amdgcn_ballot_w64(!ready);
+    const uint64_t upto = pm ? pm ^ (pm - 1u) : ~0ull;  // lanes to the nearest prefix
+    if (!(late & upto)) {
+      part += (upto >> L & 1u) ? st_val(s) : 0u;
+      if (pm) break;
+      top -= lanes;
+      s = lb_request(top, status, sst, tag);
+      continue;
     }
-    const uint32_t flag = st_flag(s), val = st_val(s);
-    const uint32_t pm = ballot(flag == ST_PREFIX);
-    if (pm) {
-      const int p = __builtin_ctz(pm);
-      run += warp_sum_u32(l <= p ? val : 0u);
+    if (++spins >= MAX_SPIN || ((spins & 1023u) == 0u && ld_dev32(&hdr[HDR_ERR]) == tag)) {
+      st_dev32(&hdr[HDR_ERR], tag);  // give up: result invalid, kernel still ends
       break;
     }
-    run += warp_sum_u32(val);
-    top -= 32;
-    s = top - l >= 0 ? ld_dev(&status[(top - l) * sst]) : st_pack(tag, ST_PREFIX, 0u);
+    __builtin_amdgcn_s_sleep(4);
+    if (!ready) s = lb_request(top, status, sst, tag);
   }
-  if (l == 0) st_dev(&status[c * sst], st_pack(tag, ST_PREFIX, agg + run));
+  const uint32_t half = warp_sum_u32(part);
+  uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)half, 0);
+  if (lanes == 64) run += (uint32_t)__builtin_amdgcn_readlane((int)half, 32);
+  if (L == 0) st_dev(&status[c * sst], st_pack(tag, ST_PREFIX, agg + run));
   return run;
 }
 
@@ -145,6 +157,7 @@ __global__ __launch_bounds__(1024) void k_lookback(const int32_t *__restrict__ x
   const int w = threadIdx.x >> 5, l = threadIdx.x & 31;
   const int64_t S = (int64_t)blockDim.x * K;
   const int64_t nfull = n / S;
+  const int lanes = lb_lanes(S);
   if (threadIdx.x == 0) {
     s_epoch = ld_epoch(hdr);
     s_tk[0] = add_dev32(&hdr[HDR_TICKET], 1u);
@@ -241,20 +254,20 @@ __global__ __launch_bounds__(1024) void k_lookback(const int32_t *__restrict__ x
     // that waiting for the window does not also wait for the prefetch
     uint32_t wa = 0u, wincl = 0u, agg = 0u;
     uint64_t first = 0;
-    if (w == 0) {
+    if ((int)threadIdx.x < lanes) {
       wa = l < W ? s_w[l] : 0u;
       wincl = warp_incl_scan_u32(wa);
       agg = (uint32_t)bcast31((int)wincl);
-      first = lookback_begin(c, agg, status, sst, tag);
+      first = lookback_begin(c, agg, nch, S, status, sst, tag);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (full) load_full(cn, nxt, cn >= nfull);
     __builtin_amdgcn_sched_barrier(0);
-    if (w == 0) {
-      const uint32_t pre = lookback_end(c, agg, first, status, sst, tag, hdr);
-      if (l < W) s_w[l] = pre + (wincl - wa);
+    if ((int)threadIdx.x < lanes) {
+      const uint32_t pre = lookback_end(c, agg, first, lanes, status, sst, tag, hdr);
+      if (w == 0 && l < W) s_w[l] = pre + (wincl - wa);
       if constexpr (MODE == MODE_COMPACT)
-        if (c == nch - 1 && l == 0) *count = (long long)pre + (long long)agg;
+        if (c == nch - 1 && threadIdx.x == 0) *count = (long long)pre + (long long)agg;
     }
     __syncthreads();
     const uint32_t off = s_w[w];
