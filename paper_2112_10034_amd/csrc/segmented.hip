@@ -475,30 +475,34 @@ __device__ __forceinline__ void seg_map_one(const SegWS &ws, const SegDesc &e, u
 }
 
 // The whole setup in one kernel, for at most SETUP1_MAX segments.  Block b
-// places segments [256b, 256b + 256); to know where they go it counts all
+// places segments [b OWN, b OWN + OWN); to know where they go it counts all
 // segments itself (at most 15 a thread, coalesced), so no block waits for
 // another and no launch separates counting, placing and descriptors.  Bound
 // by latency: each of the three kernels it replaces is one chain of launch,
 // loads and scans; together they took 21.2 us before a 10,000-segment call's
-// fused kernel and 17.8 us before a 300-segment one's, this one takes 12.9
-// and 9.7 us (plus two launches less).  Past SETUP1_MAX a thread would count
+// fused kernel and 17.8 us before a 300-segment one's, this one takes 9.5
+// and 5.7 us (plus two launches less).  OWN is small so that many blocks write
+// the long segments' descriptors; each one more counts all segments once more
+// (a fused call's us with 256 / 128 / 64 / 32: 300 segments 31.9 / 29.9 / 28.5 /
+// 28.0, 3,000 117.9 / 116.0 / 114.5 / 113.9, 10,000 302 / 299.4 / 298.5 / 301.7;
+// so 32 up to 4096 segments, then 64).  Past SETUP1_MAX a thread would count
 // more than 15 segments (their classes are counted in four bits), the
 // repeated count grows with nseg^2 / 256, and the three kernels take over.
-constexpr int SETUP1_OWN = 256, SETUP1_MAX = 15 * 1024;
-template <int DT>
+constexpr int SETUP1_MAX = 15 * 1024;
+template <int DT, int OWN>
 __global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__ off, int nseg, int64_t n, int shS,
                                                      int W, uint32_t maxch, SegWS ws, void *seg_total,
                                                      long long *seg_count) {
   // rows: total chunks, chunks before this block, then the short segments
   // per class, two classes to a word: all of them, those before this block
   __shared__ uint32_t s_x[10][32], s_sum[10];
-  __shared__ uint32_t s_w[5][SETUP1_OWN / 32];  // this block's warps: chunks, classes
-  __shared__ SegDesc s_long[SETUP1_OWN];
+  __shared__ uint32_t s_w[5][OWN / 32];  // this block's warps: chunks, classes
+  __shared__ SegDesc s_long[OWN];
   __shared__ uint32_t s_nlong;
   const int t = threadIdx.x, w = t >> 5, l = t & 31;
   const int ncls = W < MAX_CLS ? W : MAX_CLS;
   const int64_t S = (int64_t)1 << shS;
-  const int b0 = blockIdx.x * SETUP1_OWN;
+  const int b0 = blockIdx.x * OWN;
   if (t == 0) s_nlong = 0u;
   auto bounds = [&](int s, int64_t &a, int64_t &b) {
     a = off[s < nseg ? s : nseg];
@@ -517,9 +521,9 @@ __global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__
   auto chunks_of = [&](int64_t len) { return len > S ? (uint32_t)((len + S - 1) >> shS) : 0u; };
   auto is_short = [&](int64_t len) { return (uint64_t)(len - 1) < (uint64_t)S; };
   auto class_of = [&](int64_t len) { return (uint32_t)(len - 1) >> (shS - shN); };
-  // this thread's own segment (threads below SETUP1_OWN)
+  // this thread's own segment (threads below OWN)
   const int s = b0 + t;
-  const bool own = t < SETUP1_OWN && s < nseg;
+  const bool own = t < OWN && s < nseg;
   int64_t a = 0, b = 0;
   bounds(own ? s : nseg, a, b);
   // counts of all segments, classes four bits each (at most 15 segments a
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__
     mine[h] = shrt && (cls >> 1) == h ? 1u << (16 * (cls & 1)) : 0u;
     inc[h] = setup_scan32(mine[h]);
   }
-  if (t < SETUP1_OWN && l == 31) {
+  if (t < OWN && l == 31) {
     s_w[0][w] = ci;
 #pragma unroll
     for (int h = 0; h < 4; h++) s_w[1 + h][w] = inc[h];
@@ -610,7 +614,7 @@ __global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__
   if (own) {
     uint32_t ex = s_sum[1];  // chunks before this segment
 #pragma unroll
-    for (int j = 0; j < SETUP1_OWN / 32; j++) ex = sat_add(ex, j < w ? s_w[0][j] : 0u);
+    for (int j = 0; j < OWN / 32; j++) ex = sat_add(ex, j < w ? s_w[0][j] : 0u);
     ex = sat_add(ex, l == 0 ? 0u : cup);
     ws.done[s] = 0u;
     SegDesc d;
@@ -632,7 +636,7 @@ __global__ __launch_bounds__(1024) void k_seg_setup1(const int64_t *__restrict__
       for (int k = 0; k < 4; k++) mh = k == h ? inc[k] - mine[k] : mh;
       pos += (mh >> sh) & 0xffffu;
 #pragma unroll
-      for (int j = 0; j < SETUP1_OWN / 32; j++) pos += j < w ? (s_w[1 + h][j] >> sh) & 0xffffu : 0u;
+      for (int j = 0; j < OWN / 32; j++) pos += j < w ? (s_w[1 + h][j] >> sh) & 0xffffu : 0u;
       if (pos < (uint32_t)nseg) ws.sdesc[pos] = d;
     } else if (cnt) {
       const uint32_t lo = ex < maxch ? ex : maxch, e = sat_add(ex, cnt);
@@ -1569,8 +1573,10 @@ static cox_status seg_prepare(const void *x, cox_dtype dt, const int64_t *offset
 template <int DT>
 static cox_status seg_setup(const SegCall &sc, int shS, void *tot, long long *cnt, hipStream_t st) {
   if (sc.nseg <= SETUP1_MAX) {
-    hipLaunchKernelGGL(k_seg_setup1<DT>, dim3((unsigned)((sc.nseg + SETUP1_OWN - 1) / SETUP1_OWN)), dim3(1024), 0, st,
-                       sc.off, (int)sc.nseg, sc.n, shS, sc.sg.W, sc.maxch, sc.ws, tot, cnt);
+    const int own = sc.nseg <= 4096 ? 32 : 64;
+    hipLaunchKernelGGL((own == 32 ? k_seg_setup1<DT, 32> : k_seg_setup1<DT, 64>),
+                       dim3((unsigned)((sc.nseg + own - 1) / own)), dim3(1024), 0, st, sc.off, (int)sc.nseg, sc.n, shS,
+                       sc.sg.W, sc.maxch, sc.ws, tot, cnt);
     return launch_status();
   }
   // setup blocks: about 2048 segments each, at most SETUP_BLOCKS
