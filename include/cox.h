@@ -219,6 +219,16 @@ cox_status cox_warp_dot(const void *a, const void *b, cox_dtype dtype, int64_t n
                         const cox_cfg *cfg, void *chunk_partials, double *total, void *ws,
                         size_t ws_bytes, void *stream);
 
+/* cox_warp_reduce (y NULL) or cox_warp_dot (x, y) with block `away_block`
+ * of the grid starting about a millisecond late and the waiting block
+ * polling at most `polls` times (0 .. 512, the library's own limit): a check
+ * that the total and the workspace do not depend on when blocks start, as
+ * beside another stream's long kernel (no passage of the paper).  Arguments
+ * otherwise as there; COX_ERR_INVALID for a negative block. */
+cox_status cox_warp_reduce_away(const void *x, const void *y, cox_dtype dtype, int64_t n, cox_acc acc,
+                                const cox_cfg *cfg, void *chunk_partials, void *total, int32_t away_block,
+                                uint32_t polls, void *ws, size_t ws_bytes, void *stream);
+
 /* Inclusive int32 scan (the shuffle scan of the CUDA sample whose
  * shfl_scan_test and uniform_add kernels Table 1 lists; shfl_up is one of
  * the warp shuffles of Sec. 2.2.1), y_i = (x_0 + ... + x_i) mod 2^32, in

@@ -64,6 +64,8 @@ _SIGS = {
     "cox_warp_reduce_blocks_i32": (_I, [_P, _I64, _P, _P, _P]),
     "cox_warp_reduce": (_I, [_P, _I, _I64, _I, C.POINTER(cox_cfg), _P, _P, _P, _SZ, _P]),
     "cox_warp_dot": (_I, [_P, _P, _I, _I64, _I, C.POINTER(cox_cfg), _P, _P, _P, _SZ, _P]),
+    "cox_warp_reduce_away": (_I, [_P, _P, _I, _I64, _I, C.POINTER(cox_cfg), _P, _P, C.c_int32, C.c_uint32, _P, _SZ,
+                                  _P]),
     "cox_warp_scan": (_I, [_P, _P, _I64, C.POINTER(cox_cfg), _P, _SZ, _P]),
     "cox_warp_scan_noalloc": (_I, [_P, _P, _I64, C.POINTER(cox_cfg), _P, _P]),
     "cox_ballot_compact": (_I, [_P, _I64, _P, _P, C.POINTER(cox_cfg), _P, _SZ, _P]),
@@ -378,6 +380,29 @@ def warp_dot(a, b, acc=PLAIN, cfg=None, partials=True, total=None, partials_out=
     ws = workspace(OP_DOT, dt, n, cfg=cfg, device=a.device)
     _check(lib().cox_warp_dot(_ptr(a), _ptr(b), dt, n, int(acc), _cfgp(cfg), _ptr(part), _ptr(total),
                               _ptr(ws.tensor), ws.nbytes, _stream()), "cox_warp_dot")
+    return total, part
+
+
+def warp_reduce_away(x, y=None, acc=PLAIN, cfg=None, away_block=0, polls=0):
+    """warp_reduce (or warp_dot with y) with one block starting late and a
+    small bound on the wait for it."""
+    dt = _dtype_code(x)
+    op = OP_REDUCE if y is None else OP_DOT
+    _need(x, x.dtype, "x")
+    if y is not None:
+        _need(y, x.dtype, "y")
+        if x.numel() != y.numel():
+            raise ValueError("x and y differ in size")
+    n = x.numel()
+    integer = dt == I32
+    total = torch.empty(1, dtype=torch.int64 if integer else torch.float64, device=x.device)
+    nch = _nchunks(n, cfg, op, dt)
+    part = torch.empty((nch, 2) if acc == TWOSUM else (nch,), dtype=torch.int32 if integer else torch.float32,
+                       device=x.device)
+    ws = workspace(op, dt, n, cfg=cfg, device=x.device)
+    _check(lib().cox_warp_reduce_away(_ptr(x), _ptr(y), dt, n, int(acc), _cfgp(cfg), _ptr(part), _ptr(total),
+                                      int(away_block), int(polls), _ptr(ws.tensor), ws.nbytes, _stream()),
+           "cox_warp_reduce_away")
     return total, part
 
 

@@ -10,7 +10,7 @@ namespace cox {
 
 // ---------------------------------------------------------------- workspace
 // First 256 bytes: header words; data (status words / partials) follows.
-enum : int { HDR_TICKET = 0, HDR_EPOCH = 1, HDR_ERR = 3, HDR_WORDS = 64 };
+enum : int { HDR_TICKET = 0, HDR_EPOCH = 1, HDR_ERR = 3, HDR_HAND = 8, HDR_WORDS = 64 };
 constexpr size_t WS_HEADER = 256;
 
 // HDR_ERR holds the tag of a call whose bounded wait gave up; ERR_LAYOUT
@@ -64,10 +64,34 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 // 512-block segmented call and 2 % of a 2^28-element scan (0.356 -> 0.349 ms).
 __device__ __forceinline__ uint32_t ld_epoch(const uint32_t *hdr) { return ld_dev32(&hdr[HDR_EPOCH]); }
 
-// spin bound of every cross-block wait (well under a second); a wait that
-// runs out, or that sees another wait's failure, sets HDR_ERR and proceeds,
-// so no kernel can hang
+// Spin bound of the waits for blocks that hold a ticket and so have started
+// (look-backs; a second or so).  One that runs out, or that sees another
+// wait's failure, sets HDR_ERR and proceeds, so no kernel can hang.
 constexpr uint32_t MAX_SPIN = 1u << 20;
+
+// A block that finishes a call for all others (k_reduce's combine, k_once's
+// epoch) waits for words of blocks that another stream's kernel may keep from
+// starting for any time.  So it polls HAND_POLLS times (some hundred
+// microseconds) and then hands the call over: it puts the call's tag into
+// HDR_HAND, looks at the words once more, and leaves if one is missing.
+// Every block reads HDR_HAND when its own words have arrived; one that finds
+// the tag there looks at all words.  The block whose words arrive last either
+// reads HDR_HAND after it was set, and then sees all words, or before, and
+// then the waiting block's second look sees them all.  Whoever does takes the
+// call (hand_taken: one block only) and finishes it.  So the epoch, which
+// every block reads before it publishes, never advances ahead of a block.
+constexpr uint32_t HAND_POLLS = 512;
+// how long the block named by a test's entry point stays away: about a
+// millisecond, several times HAND_POLLS
+__device__ __forceinline__ void stay_away() {
+  for (int i = 0; i < 300; i++) __builtin_amdgcn_s_sleep(127);
+}
+// one thread of a block that has seen every word
+__device__ __forceinline__ bool hand_taken(uint32_t *hdr, uint32_t tag) {
+  uint32_t want = tag;
+  return __hip_atomic_compare_exchange_strong(&hdr[HDR_HAND], &want, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Streaming (non-temporal) 16/8/4-byte loads and stores.  Data that is
 // read or written once per call bypasses the cache hierarchy's retention;

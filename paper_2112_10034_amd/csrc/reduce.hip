@@ -12,10 +12,11 @@
 // last block, once it has published its own, collects the words, waiting for
 // each one's tag, and runs the FP64 (or int64) final combine.  A single
 // chunk's value is the total at once.  No memory fences are needed: a word
-// with the current tag can only hold this call's partial, and the last block
-// advances the epoch only after it has seen every block's words, whose tags
-// every block derived from its own read of the epoch.  Nobody but that one
-// block waits, so all others end whatever order they run in.  (With a counter
+// with the current tag can only hold this call's partial, and the epoch
+// advances only after every block's words were seen, whose tags every block
+// derived from its own read of the epoch.  A wait that takes too long ends
+// with the combine handed over to the block that publishes last (HDR_HAND), so
+// the total does not depend on when blocks start.  (With a counter
 // of finished blocks, the last of which combines, one or two more round trips
 // lay between: sums of 2^20 / 2^24 / 2^28 float32 8.4 / 17.6 / 162.7 us, 6.3 /
 // 16.0 / 161.2 now; dot of 2^28 330.6 and 320.)
@@ -268,30 +269,27 @@ __device__ __forceinline__ void store_partial(void *part, uint64_t *pw, uint32_t
   }
 }
 
-// a tagged word that did not yet carry `tag` when first read: wait for it
-// (bounded, by more than a second: the block that publishes it may still wait
-// behind another stream's kernel; running out sets HDR_ERR)
-__device__ __noinline__ uint64_t wait_word(const uint64_t *p, uint32_t tag, uint32_t *hdr) {
-  uint64_t s = ld_dev(p);
-  uint32_t spins = 0;
-  while ((uint32_t)(s >> 32) != tag) {
-    if (++spins >= MAX_SPIN) {
-      st_dev32(&hdr[HDR_ERR], tag);
-      break;
-    }
+// a tagged word that did not yet carry `tag` when first read: at most `polls`
+// more readings; the caller looks at the tag of what comes back
+__device__ __noinline__ uint64_t wait_word(const uint64_t *p, uint32_t tag, uint32_t polls) {
+  uint64_t s = 0;
+  for (uint32_t spins = 0; spins < polls; spins++) {
+    s = ld_dev(p);
+    if ((uint32_t)(s >> 32) == tag) break;
     if (spins < 256) __builtin_amdgcn_s_sleep(1);
     else __builtin_amdgcn_s_sleep(32);
-    s = ld_dev(p);
   }
   return s;
 }
 
 // value bits of FB tagged words p[i0 + b*stride] (b < FB, index < lim):
 // all loads are issued first, then any word not yet carrying the tag is
-// waited for; out-of-range entries get `pad`
+// waited for (late: one did not come; the rest is not waited for);
+// out-of-range entries get `pad`
 template <int FB>
 __device__ __forceinline__ void take_words(const uint64_t *p, int64_t i0, int64_t stride, int64_t lim,
-                                           uint32_t tag, uint32_t *hdr, uint32_t pad, uint32_t (&out)[FB]) {
+                                           uint32_t tag, uint32_t polls, bool &late, uint32_t pad,
+                                           uint32_t (&out)[FB]) {
   uint64_t w[FB];
 #pragma unroll
   for (int b = 0; b < FB; b++) {
@@ -301,9 +299,19 @@ __device__ __forceinline__ void take_words(const uint64_t *p, int64_t i0, int64_
 #pragma unroll
   for (int b = 0; b < FB; b++) {
     const int64_t i = i0 + (int64_t)b * stride;
-    if ((uint32_t)(w[b] >> 32) != tag) w[b] = wait_word(&p[i], tag, hdr);
+    if ((uint32_t)(w[b] >> 32) != tag) {
+      w[b] = wait_word(&p[i], tag, late ? 0u : polls);
+      late = late || (uint32_t)(w[b] >> 32) != tag;
+    }
     out[b] = (uint32_t)w[b];
   }
+}
+
+// whether words [0, nw) all carry the tag (every thread of the block)
+__device__ __forceinline__ bool words_there(const uint64_t *p, int64_t nw, uint32_t tag) {
+  int missing = 0;
+  for (int64_t i = threadIdx.x; i < nw; i += blockDim.x) missing |= (uint32_t)(ld_dev(&p[i]) >> 32) != tag;
+  return !__syncthreads_or(missing);
 }
 
 // Full chunks c = first + i * gridDim.x run double-buffered: the next
@@ -318,7 +326,8 @@ __device__ __forceinline__ void take_words(const uint64_t *p, int64_t i0, int64_
 template <int K, int DT, int OP, int ACC>
 __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, const void *__restrict__ y,
                                                  int64_t n, int64_t nch, void *__restrict__ part,
-                                                 void *__restrict__ total, uint32_t *__restrict__ hdr) {
+                                                 void *__restrict__ total, uint32_t *__restrict__ hdr,
+                                                 uint32_t polls, int away) {
   constexpr int ESZ = ElemT<DT>::size;
   constexpr int V = K < 16 / ESZ ? K : 16 / ESZ;
   constexpr int R = K / V;
@@ -328,8 +337,9 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   constexpr uint32_t XPAD = DT == DT_I32 ? 0u : DT == DT_BF16 ? 0x80008000u : 0x80000000u;
   __shared__ Acc slot[2][32];
   __shared__ double fin[256];
-  __shared__ uint32_t s_epoch;
+  __shared__ uint32_t s_epoch, s_late, s_go;
 
+  if ((int)blockIdx.x == away) stay_away();
   const int W = blockDim.x >> 5;
   uint64_t *pw = (uint64_t *)(hdr + HDR_WORDS);
   // thread 0 stores the partials, so it alone needs the epoch until the
@@ -471,10 +481,19 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   }
   if (single) return;
 
-  // the grid's last block combines the chunk partials
-  if (blockIdx.x != gridDim.x - 1) return;
-  if (threadIdx.x == 0) s_epoch = epoch;
+  // the grid's last block combines the chunk partials, or the block that it
+  // was handed over to
+  const bool last = blockIdx.x == gridDim.x - 1;
+  if (threadIdx.x == 0) {
+    s_epoch = epoch;
+    s_late = 0u;
+    if (!last) {
+      wait_stores();
+      s_go = ld_dev32(&hdr[HDR_HAND]) == tag_of_epoch(epoch) ? 1u : 0u;
+    }
+  }
   __syncthreads();
+  if (!last && !s_go) return;
   epoch = s_epoch;
   const uint32_t tag = tag_of_epoch(epoch);
 
@@ -482,91 +501,117 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   // thread before they are added, so the fixed serial order costs one
   // memory latency per batch rather than one per chunk.
   constexpr int FB = ACC == COX_ACC_PLAIN ? 32 : 8;  // TwoSum: two words a chunk, and no spills
-  if constexpr (DT == DT_I32) {
-    __shared__ long long isum[32];
-    long long s = 0;
-    auto batch = [&](auto fb, int64_t c0) {
-      constexpr int B = decltype(fb)::value;
-      uint32_t buf[B];
-      take_words<B>(pw, c0, blockDim.x, nch, tag, hdr, 0u, buf);
-#pragma unroll
-      for (int b = 0; b < B; b++) s += (long long)(int32_t)buf[b];
-    };
-    if (nch <= blockDim.x) batch(std::integral_constant<int, 1>{}, threadIdx.x);
-    else
-      for (int64_t c0 = threadIdx.x; c0 < nch; c0 += (int64_t)FB * blockDim.x)
-        batch(std::integral_constant<int, FB>{}, c0);
-    // block sum of int64 (order does not matter for integers)
-    s = tree_i64(s);
-    if (l == 0) isum[w] = s;
-    __syncthreads();
-    if (threadIdx.x < 32) {
-      long long tot = l < W ? isum[l] : 0;
-      tot = tree_i64(tot);
-      if (l == 0) {
-        *(long long *)total = tot;
-        st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
-      }
+  for (bool handed = !last;;) {
+    if (handed) {
+      if (!words_there(pw, ACC == COX_ACC_PLAIN ? nch : 2 * nch, tag)) return;
+      if (threadIdx.x == 0) s_go = hand_taken(hdr, tag) ? 1u : 0u;
+      __syncthreads();
+      if (!s_go) return;
     }
-  } else {
-    // FP64 final tree shaped like a 256-thread block (see cox.h); a chain
-    // padded with -0.0 at its end is unchanged
-    for (int j = threadIdx.x; j < 256; j += blockDim.x) {
-      double s = -0.0;
+    bool late = false;
+    if constexpr (DT == DT_I32) {
+      __shared__ long long isum[32];
+      long long s = 0;
       auto batch = [&](auto fb, int64_t c0) {
         constexpr int B = decltype(fb)::value;
-        double buf[B];
-        if constexpr (ACC == COX_ACC_PLAIN) {
-          uint32_t v[B];
-          take_words<B>(pw, c0, 256, nch, tag, hdr, 0x80000000u, v);
+        uint32_t buf[B];
+        take_words<B>(pw, c0, blockDim.x, nch, tag, polls, late, 0u, buf);
 #pragma unroll
-          for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)v[b]);
-        } else {
-          // words 2c (s) and 2c + 1 (c); padding (-0.0, -0.0) adds -0.0
-          uint32_t vs[B], vc[B];
-          take_words<B>(pw, 2 * c0, 512, 2 * nch, tag, hdr, 0x80000000u, vs);
-          take_words<B>(pw, 2 * c0 + 1, 512, 2 * nch, tag, hdr, 0x80000000u, vc);
-#pragma unroll
-          for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)vs[b]) + (double)i2f((int)vc[b]);
-        }
-#pragma unroll
-        for (int b = 0; b < B; b++) s = s + buf[b];
+        for (int b = 0; b < B; b++) s += (long long)(int32_t)buf[b];
       };
-      if (nch <= 256) batch(std::integral_constant<int, 1>{}, j);
+      if (nch <= blockDim.x) batch(std::integral_constant<int, 1>{}, threadIdx.x);
       else
-        for (int64_t c0 = j; c0 < nch; c0 += (int64_t)FB * 256) batch(std::integral_constant<int, FB>{}, c0);
-      // the tree of each group of 32, by its own warp where there are eight
-      if (blockDim.x >= 256) {
-        s = tree_f64(s);
-        if (l == 0) fin[j >> 5] = s;
-      } else {
-        fin[j] = s;
+        for (int64_t c0 = threadIdx.x; c0 < nch; c0 += (int64_t)FB * blockDim.x)
+          batch(std::integral_constant<int, FB>{}, c0);
+      // block sum of int64 (order does not matter for integers)
+      s = tree_i64(s);
+      if (l == 0) isum[w] = s;
+      if (late) s_late = 1u;
+      __syncthreads();
+      if (!s_late) {
+        if (threadIdx.x < 32) {
+          long long tot = l < W ? isum[l] : 0;
+          tot = tree_i64(tot);
+          if (l == 0) {
+            *(long long *)total = tot;
+            st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
+          }
+        }
+        return;
       }
+    } else {
+      // FP64 final tree shaped like a 256-thread block (see cox.h); a chain
+      // padded with -0.0 at its end is unchanged
+      for (int j = threadIdx.x; j < 256; j += blockDim.x) {
+        double s = -0.0;
+        auto batch = [&](auto fb, int64_t c0) {
+          constexpr int B = decltype(fb)::value;
+          double buf[B];
+          if constexpr (ACC == COX_ACC_PLAIN) {
+            uint32_t v[B];
+            take_words<B>(pw, c0, 256, nch, tag, polls, late, 0x80000000u, v);
+#pragma unroll
+            for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)v[b]);
+          } else {
+            // words 2c (s) and 2c + 1 (c); padding (-0.0, -0.0) adds -0.0
+            uint32_t vs[B], vc[B];
+            take_words<B>(pw, 2 * c0, 512, 2 * nch, tag, polls, late, 0x80000000u, vs);
+            take_words<B>(pw, 2 * c0 + 1, 512, 2 * nch, tag, polls, late, 0x80000000u, vc);
+#pragma unroll
+            for (int b = 0; b < B; b++) buf[b] = (double)i2f((int)vs[b]) + (double)i2f((int)vc[b]);
+          }
+#pragma unroll
+          for (int b = 0; b < B; b++) s = s + buf[b];
+        };
+        if (nch <= 256) batch(std::integral_constant<int, 1>{}, j);
+        else
+          for (int64_t c0 = j; c0 < nch; c0 += (int64_t)FB * 256) batch(std::integral_constant<int, FB>{}, c0);
+        // the tree of each group of 32, by its own warp where there are eight
+        if (blockDim.x >= 256) {
+          s = tree_f64(s);
+          if (l == 0) fin[j >> 5] = s;
+        } else {
+          fin[j] = s;
+        }
+      }
+      if (late) s_late = 1u;
+      __syncthreads();
+      if (!s_late) {
+        if (threadIdx.x < 32) {
+          double top = -0.0;
+          if (blockDim.x >= 256) {
+            if (l < 8) top = fin[l];
+          } else {
+#pragma unroll 1
+            for (int vw = 0; vw < 8; vw++) {
+              const double r = tree_f64(fin[32 * vw + l]);
+              const double r0 = __shfl(r, 0, 32);
+              if (l == vw) top = r0;
+            }
+          }
+          top = tree_f64(top);
+          if (l == 0) {
+            *(double *)total = top;
+            st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
+          }
+        }
+        return;
+      }
+    }
+    // a word did not come in time
+    __syncthreads();  // s_late and the sums are written again
+    if (threadIdx.x == 0) {
+      s_late = 0u;
+      st_dev32(&hdr[HDR_HAND], tag);
+      wait_stores();
     }
     __syncthreads();
-    if (threadIdx.x < 32) {
-      double top = -0.0;
-      if (blockDim.x >= 256) {
-        if (l < 8) top = fin[l];
-      } else {
-#pragma unroll 1
-        for (int vw = 0; vw < 8; vw++) {
-          const double r = tree_f64(fin[32 * vw + l]);
-          const double r0 = __shfl(r, 0, 32);
-          if (l == vw) top = r0;
-        }
-      }
-      top = tree_f64(top);
-      if (l == 0) {
-        *(double *)total = top;
-        st_dev32(&hdr[HDR_EPOCH], epoch + 1u);
-      }
-    }
+    handed = true;
   }
 }
 
 // ---------------------------------------------------------------- dispatch
-using reduce_fn = void (*)(const void *, const void *, int64_t, int64_t, void *, void *, uint32_t *);
+using reduce_fn = void (*)(const void *, const void *, int64_t, int64_t, void *, void *, uint32_t *, uint32_t, int);
 
 template <int DT, int OP, int ACC>
 static reduce_fn pick_k(int k) {
@@ -601,7 +646,7 @@ static int reduce_blocks_per_cu(int block) { return block >= 512 ? 1 : 512 / blo
 
 static cox_status reduce_any(const void *x, const void *y, cox_dtype dtype, int op, int64_t n, cox_acc acc,
                              const cox_cfg *cfg, void *chunk_partials, void *total, void *ws,
-                             size_t ws_bytes, void *stream) {
+                             size_t ws_bytes, void *stream, uint32_t polls = HAND_POLLS, int away = -1) {
   if (n < 0 || !total) return COX_ERR_INVALID;
   if (acc != COX_ACC_PLAIN && acc != COX_ACC_TWOSUM) return COX_ERR_DTYPE;
   if (dtype != COX_I32 && dtype != COX_F32 && dtype != COX_BF16) return COX_ERR_DTYPE;
@@ -621,7 +666,7 @@ static cox_status reduce_any(const void *x, const void *y, cox_dtype dtype, int 
   void *part = chunk_partials;  // optional plain copy; tagged words live in the workspace
   const int grid = persistent_grid((const void *)fn, block, nch > 0 ? nch : 1, sg.G, 0, reduce_blocks_per_cu(block));
   hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, (hipStream_t)stream, x, y, n, nch, part, total,
-                     (uint32_t *)ws);
+                     (uint32_t *)ws, polls, away);
   return launch_status();
 }
 
@@ -657,6 +702,15 @@ cox_status cox_warp_dot(const void *a, const void *b, cox_dtype dtype, int64_t n
                         void *stream) {
   if (dtype != COX_F32 && dtype != COX_BF16) return COX_ERR_DTYPE;
   return reduce_any(a, b, dtype, OP_DOT, n, acc, cfg, chunk_partials, total, ws, ws_bytes, stream);
+}
+
+cox_status cox_warp_reduce_away(const void *x, const void *y, cox_dtype dtype, int64_t n, cox_acc acc,
+                                const cox_cfg *cfg, void *chunk_partials, void *total, int32_t away_block,
+                                uint32_t polls, void *ws, size_t ws_bytes, void *stream) {
+  if (away_block < 0 || polls > HAND_POLLS) return COX_ERR_INVALID;
+  if (y && dtype != COX_F32 && dtype != COX_BF16) return COX_ERR_DTYPE;
+  return reduce_any(x, y, dtype, y ? OP_DOT : OP_SUM, n, acc, cfg, chunk_partials, total, ws, ws_bytes, stream, polls,
+                    away_block);
 }
 
 }  // extern "C"

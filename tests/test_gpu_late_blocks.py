@@ -1,0 +1,66 @@
+"""Reductions whose blocks do not all start together: the total, the chunk
+partials and the workspace's next calls are those of an ordinary call,
+however late a block starts and however short the wait for it is."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+
+    from paper_2112_10034_amd import cox
+
+    cox.lib()
+    return torch, cox
+
+
+def same(torch, a, b):
+    return all(torch.equal(u.view(torch.uint8), v.view(torch.uint8)) for u, v in zip(a, b))
+
+
+# (schedule, chunks): two blocks; a ragged last chunk; more chunks than the 256
+# lanes of the final tree; several chunks a block and a combine of blocks below
+# and above 256 threads
+SHAPES = [((4, 4, 0), 2), ((1, 1, 0), 37), ((4, 4, 0), 300), ((8, 32, 64), 700), ((2, 2, 5), 91)]
+
+
+@pytest.mark.parametrize("polls", [0, 3, 512])
+@pytest.mark.parametrize("cfg,nch", SHAPES)
+@pytest.mark.parametrize("dtype,acc,dot", [("int32", 0, False), ("float32", 0, False), ("bfloat16", 1, False),
+                                           ("float32", 1, True), ("bfloat16", 0, True)])
+def test_reduce_with_a_late_block(dev, dtype, acc, dot, cfg, nch, polls):
+    torch, cox = dev
+    S = 32 * cfg[0] * cfg[1]
+    n = nch * S - S // 3
+    g = torch.Generator(device="cuda").manual_seed(nch + polls)
+
+    def draw():
+        if dtype == "int32":
+            return torch.randint(-1 << 20, 1 << 20, (n,), dtype=torch.int32, device="cuda", generator=g)
+        return torch.randn(n, device="cuda", generator=g).to(getattr(torch, dtype))
+
+    def ordinary(x, y):
+        return cox.warp_reduce(x, acc, cfg=cfg) if y is None else cox.warp_dot(x, y, acc, cfg=cfg)
+
+    blocks = min(nch, cfg[2] or 1 << 30)
+    ws = cox.workspace(cox.OP_DOT if dot else cox.OP_REDUCE, cox._CODES[getattr(torch, dtype)], n, cfg=cfg)
+    for away in sorted({0, blocks // 2, blocks - 1}):
+        x1, x2 = draw(), draw()
+        y1, y2 = (draw(), draw()) if dot else (None, None)
+        want1, want2 = ordinary(x1, y1), ordinary(x2, y2)
+        got = cox.warp_reduce_away(x1, y1, acc, cfg, away, polls)
+        after = ordinary(x2, y2)
+        assert same(torch, got, want1), away
+        assert same(torch, after, want2), away
+        ws.status()
+
+
+def test_refuses_a_negative_block(dev):
+    torch, cox = dev
+    x = torch.ones(4096, dtype=torch.int32, device="cuda")
+    for kw in ({"away_block": -1}, {"polls": 513}):
+        with pytest.raises(cox.CoxError) as e:
+            cox.warp_reduce_away(x, **kw)
+        assert e.value.code == 1
