@@ -277,6 +277,17 @@ cox_status cox_warp_scan_noalloc(const int32_t *x, int32_t *y, int64_t n, const 
 cox_status cox_ballot_compact(const int32_t *x, int64_t n, int32_t *out, int64_t *count,
                               const cox_cfg *cfg, void *ws, size_t ws_bytes, void *stream);
 
+/* cox_warp_scan and cox_ballot_compact of a short input under the default
+ * schedule (the sizes that take one chunk per block; COX_ERR_UNSUPPORTED for
+ * others), with block `away_block` starting about a millisecond late and the
+ * other blocks polling its word at most `polls` times (0 .. 512, the library's
+ * own limit): a check that results and the workspace do not depend on when
+ * blocks start (no passage of the paper).  x and the output must not overlap. */
+cox_status cox_warp_scan_away(const int32_t *x, int32_t *y, int64_t n, int32_t away_block, uint32_t polls, void *ws,
+                              size_t ws_bytes, void *stream);
+cox_status cox_ballot_compact_away(const int32_t *x, int64_t n, int32_t *out, int64_t *count, int32_t away_block,
+                                   uint32_t polls, void *ws, size_t ws_bytes, void *stream);
+
 /* Tile sort, a workload built from the warp shuffles of Sec. 2.2.1
  * (__shfl_xor_sync exchanges) over thread-block tiles of Sec. 2.2.2:
  * sorts every group of `tile` consecutive keys ascending (unsigned) with a

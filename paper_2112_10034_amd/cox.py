@@ -69,6 +69,8 @@ _SIGS = {
     "cox_warp_scan": (_I, [_P, _P, _I64, C.POINTER(cox_cfg), _P, _SZ, _P]),
     "cox_warp_scan_noalloc": (_I, [_P, _P, _I64, C.POINTER(cox_cfg), _P, _P]),
     "cox_ballot_compact": (_I, [_P, _I64, _P, _P, C.POINTER(cox_cfg), _P, _SZ, _P]),
+    "cox_warp_scan_away": (_I, [_P, _P, _I64, C.c_int32, C.c_uint32, _P, _SZ, _P]),
+    "cox_ballot_compact_away": (_I, [_P, _I64, _P, _P, C.c_int32, C.c_uint32, _P, _SZ, _P]),
     "cox_tile_sort": (_I, [_P, _P, _I64, _I, C.POINTER(cox_cfg), _P]),
     "cox_tile_sort_kv": (_I, [_P, _P, _P, _P, _I64, _I, C.POINTER(cox_cfg), _P]),
     "cox_tile_reduce": (_I, [_P, _I64, _I, _P, _P]),
@@ -448,6 +450,29 @@ def ballot_compact(x, cfg=None, out=None, count=None):
     ws = workspace(OP_COMPACT, I32, n, cfg=cfg, device=x.device)
     _check(lib().cox_ballot_compact(_ptr(x), n, _ptr(out), _ptr(count), _cfgp(cfg), _ptr(ws.tensor),
                                     ws.nbytes, _stream()), "cox_ballot_compact")
+    return out, count
+
+
+def warp_scan_away(x, away_block=0, polls=0):
+    """warp_scan of a short input with one block starting late and a small
+    bound on the wait for it."""
+    _need(x, torch.int32, "x")
+    n, y = x.numel(), torch.empty_like(x)
+    ws = workspace(OP_SCAN, I32, n, device=x.device)
+    _check(lib().cox_warp_scan_away(_ptr(x), _ptr(y), n, int(away_block), int(polls), _ptr(ws.tensor), ws.nbytes,
+                                    _stream()), "cox_warp_scan_away")
+    return y
+
+
+def ballot_compact_away(x, away_block=0, polls=0):
+    """ballot_compact of a short input with one block starting late and a
+    small bound on the wait for it."""
+    _need(x, torch.int32, "x")
+    n, out = x.numel(), torch.empty_like(x)
+    count = torch.empty(1, dtype=torch.int64, device=x.device)
+    ws = workspace(OP_COMPACT, I32, n, device=x.device)
+    _check(lib().cox_ballot_compact_away(_ptr(x), n, _ptr(out), _ptr(count), int(away_block), int(polls),
+                                         _ptr(ws.tensor), ws.nbytes, _stream()), "cox_ballot_compact_away")
     return out, count
 
 

@@ -357,15 +357,15 @@ __global__ __launch_bounds__(1024) void k_lookback(const int32_t *__restrict__ x
 // us, 7.2 / 8.6 / 11.0 / 13.9.
 //
 // No ticket orders the blocks, so a block may wait for one that the device
-// has not started.  After ONCE_SPINS polls it therefore adds up the missing
+// has not started.  After HAND_POLLS polls it therefore adds up the missing
 // chunk from x itself (nothing writes x: the output lies apart), so every
 // block ends whatever order the blocks start in, also beside other kernels.
 // The last chunk's block advances the epoch once it has seen every other
 // block's own word: each was published by a block that has read the epoch.
-// Only that one block may wait for blocks not yet started.  (Counting the
-// started blocks with an atomic instead cost 2.4 us at 245 blocks.)
+// If one is missing for too long it leaves that to the block that publishes
+// last (HDR_HAND).  (Counting the started blocks with an atomic instead cost
+// 2.4 us at 245 blocks.)
 constexpr int ONCE_CHUNKS = 1024;
-constexpr uint32_t ONCE_SPINS = 512;  // some hundred microseconds
 
 // inclusive scan of v over the 64 lanes of the wave
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
@@ -390,13 +390,15 @@ __device__ __forceinline__ void once_wait(int nch) {
 template <int K, int BT, int MODE>
 __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *__restrict__ x, int32_t *__restrict__ out,
                                              long long *__restrict__ count, int64_t n, int nch,
-                                             uint64_t *__restrict__ status, uint32_t *__restrict__ hdr) {
+                                             uint64_t *__restrict__ status, uint32_t *__restrict__ hdr,
+                                             uint32_t polls, int away) {
   static_assert(K % 4 == 0, "rows of 16-byte vectors");
   constexpr int R = K / 4, NW = BT / 64, S = BT * K;
   __shared__ uint32_t s_w[NW], s_pre[NW], s_epoch, s_miss, s_late;
   __shared__ int32_t s_stage[MODE == MODE_COMPACT ? S + NW * 64 : 1];
   const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
   const int c = blockIdx.x;
+  if (c == away) stay_away();
   uint32_t e = 0u;
   if (t == 0 && nch > 1) {
     e = ld_epoch(hdr);
@@ -472,9 +474,9 @@ __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *
     off += j < wv ? u : 0u;
     agg += u;
   }
-  uint32_t pre = 0u;
+  uint32_t pre = 0u, tag = 0u, hand = 0u;
   if (nch > 1) {
-    const uint32_t tag = tag_of_epoch(s_epoch);
+    tag = tag_of_epoch(s_epoch);
     if (t == 0) st_dev(&status[c], st_pack(tag, ST_AGG, agg));
     once_wait(nch);
     // thread t: the aggregates of chunks t, t + BT, .. below c
@@ -486,7 +488,7 @@ __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *
 #pragma unroll
     for (int k = 0; k < NP; k++) {
       uint32_t spins = 0;
-      while (st_tag(w[k]) != tag && ++spins < ONCE_SPINS) {
+      while (st_tag(w[k]) != tag && spins++ < polls) {
         __builtin_amdgcn_s_sleep(1);
         w[k] = ld_dev(&status[t + k * BT]);
       }
@@ -534,25 +536,16 @@ __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *
         __syncthreads();
       }
       sum_words();
-      if (c == nch - 1 && late) {
-        // the epoch may move on only when these blocks have read it
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-          uint32_t spins = 0;
-          while (t + k * BT < c && st_tag(ld_dev(&status[t + k * BT])) != tag) {
-            if (++spins >= MAX_SPIN) {
-              st_dev32(&hdr[HDR_ERR], tag);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(8);
-          }
-        }
-      }
       __syncthreads();
     }
 #pragma unroll
     for (int j = 0; j < NW; j++) pre += s_pre[j];
-    if (c == nch - 1 && t == 0) st_dev32(&hdr[HDR_EPOCH], s_epoch + 1u);
+    if (c == nch - 1) {
+      if (t == 0 && !s_miss) st_dev32(&hdr[HDR_EPOCH], s_epoch + 1u);
+    } else if (t < 64) {
+      wait_stores();  // the block's word; what was polled for came after it
+      hand = ld_dev32(&hdr[HDR_HAND]);
+    }
   }
   const uint32_t at = pre + off;
   if constexpr (MODE == MODE_SCAN) {
@@ -578,9 +571,22 @@ __global__ __launch_bounds__(BT, BT == 1024 ? 8 : 1) void k_once(const int32_t *
     const uint32_t si = l < 4u ? l : hn + 4u * nv + (l - 4u);
     if (l < 4u ? l < hn : l - 4u < tn) dst[si] = region[si];
   }
+  if (nch == 1 || t >= 64) return;
+  // the epoch, if the last chunk's block did not see all words in time
+  const bool hands = c == nch - 1 && s_miss;
+  if (hands) {
+    if (t == 0) st_dev32(&hdr[HDR_HAND], tag);
+    wait_stores();
+  }
+  if (hands || hand == tag) {
+    bool missing = false;
+    for (int i = t; i < nch; i += 64) missing = missing || st_tag(ld_dev(&status[i])) != tag;
+    if (!__builtin_amdgcn_ballot_w64(missing) && t == 0 && hand_taken(hdr, tag))
+      st_dev32(&hdr[HDR_EPOCH], s_epoch + 1u);
+  }
 }
 
-using once_fn = void (*)(const int32_t *, int32_t *, long long *, int64_t, int, uint64_t *, uint32_t *);
+using once_fn = void (*)(const int32_t *, int32_t *, long long *, int64_t, int, uint64_t *, uint32_t *, uint32_t, int);
 
 // The kernel for n elements, by measurement (us per call, scan / compaction):
 //  - up to 2^18 elements 8192 a block with 1024 threads, 8 a lane: fewest
@@ -619,14 +625,14 @@ static bool disjoint(const void *a, const void *b, size_t bytes) {
 // asks for always has it); false if not.
 template <int MODE>
 static bool launch_once(const int32_t *x, int32_t *out, long long *count, int64_t n, const cox_cfg *cfg, void *ws,
-                        size_t ws_bytes, hipStream_t st, cox_status *r) {
+                        size_t ws_bytes, hipStream_t st, cox_status *r, uint32_t polls = HAND_POLLS, int away = -1) {
   if (n <= 0 || !default_schedule(cfg) || !disjoint(x, out, (size_t)n * 4)) return false;
   const OncePick p = pick_once<MODE>(n);
   if (!p.fn) return false;
   const int64_t nch = (n + p.S - 1) / p.S;
   if (nch > ONCE_CHUNKS || ws_bytes < WS_HEADER + 8 * (size_t)nch) return false;
   hipLaunchKernelGGL(p.fn, dim3((unsigned)nch), dim3(p.BT), 0, st, x, out, count, n, (int)nch,
-                     (uint64_t *)((char *)ws + WS_HEADER), (uint32_t *)ws);
+                     (uint64_t *)((char *)ws + WS_HEADER), (uint32_t *)ws, polls, away);
   *r = launch_status();
   return true;
 }
@@ -803,6 +809,30 @@ cox_status cox_ballot_compact(const int32_t *x, int64_t n, int32_t *out, int64_t
   hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds - 256, (hipStream_t)stream, x, out, (long long *)count, n,
                      nch, (uint64_t *)((char *)ws + WS_HEADER), (int64_t)ST_STRIDE, (uint32_t *)ws);
   return launch_status();
+}
+
+cox_status cox_warp_scan_away(const int32_t *x, int32_t *y, int64_t n, int32_t away_block, uint32_t polls, void *ws,
+                              size_t ws_bytes, void *stream) {
+  Sigma sg;
+  int64_t nch;
+  cox_status st = check_lookback_call(COX_OP_SCAN, n, x, nullptr, ws, ws_bytes, &sg, &nch);
+  if (st != COX_OK) return st;
+  if (away_block < 0 || polls > HAND_POLLS || !y) return COX_ERR_INVALID;
+  if (!aligned16(y)) return COX_ERR_ALIGN;
+  return launch_once<MODE_SCAN>(x, y, nullptr, n, nullptr, ws, ws_bytes, (hipStream_t)stream, &st, polls, away_block)
+             ? st : COX_ERR_UNSUPPORTED;
+}
+
+cox_status cox_ballot_compact_away(const int32_t *x, int64_t n, int32_t *out, int64_t *count, int32_t away_block,
+                                   uint32_t polls, void *ws, size_t ws_bytes, void *stream) {
+  Sigma sg;
+  int64_t nch;
+  cox_status st = check_lookback_call(COX_OP_COMPACT, n, x, nullptr, ws, ws_bytes, &sg, &nch);
+  if (st != COX_OK) return st;
+  if (away_block < 0 || polls > HAND_POLLS || !count || !out) return COX_ERR_INVALID;
+  return launch_once<MODE_COMPACT>(x, out, (long long *)count, n, nullptr, ws, ws_bytes, (hipStream_t)stream, &st, polls,
+                                   away_block)
+             ? st : COX_ERR_UNSUPPORTED;
 }
 
 }  // extern "C"
