@@ -320,9 +320,12 @@ __device__ __forceinline__ bool words_there(const uint64_t *p, int64_t nw, uint3
 // they lie in memory and elements are widened where they are used: widened at
 // the load, bfloat16 vectors took twice the registers, and the compiler
 // waited for one chunk before it requested the next (dot of 2^28 bfloat16,
-// TwoSum: 179 -> 165 us; of 2^28 float32: 373 -> 341; sum: 179 -> 162).  Past the block's last full chunk
-// the request is kept (loads stay unconditional) but every lane reads the
-// array's first vector: one line, not a chunk.
+// TwoSum: 179 -> 165 us; of 2^28 float32: 373 -> 341; sum: 179 -> 162).  Past the
+// block's last full chunk the request is kept (loads stay unconditional) but
+// every lane reads the array's first vector: one line, not a chunk.  Buffers of
+// more than 32 words a lane (32 float32 elements of two arrays) would spill (dot
+// of 2^25 in chunks of 32768 elements, plain / TwoSum: 75 / 73 us, 57 / 57 where
+// the compiler loads one at a time), so they hold half of a chunk's rows: 43 / 44.
 template <int K, int DT, int OP, int ACC>
 __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, const void *__restrict__ y,
                                                  int64_t n, int64_t nch, void *__restrict__ part,
@@ -359,26 +362,28 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   const int64_t first = blockIdx.x < 8 * per_xcd ? (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) : blockIdx.x;
 
   const int64_t nfull = n / S;
-  typedef uint32_t Buf[NA][R][NW];
-  auto load_full = [&](int64_t c, Buf &r) {
+  constexpr int PARTS = NA * R * NW > 32 ? 2 : 1, RP = R / PARTS;  // rows of a buffer
+  typedef uint32_t Buf[NA][RP][NW];
+  auto load_full = [&](int64_t c, int part, Buf &r) {
     const bool dummy = c >= nfull;
     // one base offset and one row stride per lane (not a select per load)
-    const int64_t b0 = (dummy ? 0 : c * S + (int64_t)w * 32 * K + (int64_t)l * V) * ESZ;
+    const int64_t b0 = (dummy ? 0 : c * S + (int64_t)w * 32 * K + (int64_t)(part * RP * 32 + l) * V) * ESZ;
     const int rs = dummy ? 0 : 32 * VB;
 #pragma unroll
-    for (int i = 0; i < R; i++) {
+    for (int i = 0; i < RP; i++) {
       load_raw<VB>((const char *)x + b0 + i * rs, r[0][i]);
       if constexpr (NA == 2) load_raw<VB>((const char *)y + b0 + i * rs, r[NA - 1][i]);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto reduce_chunk = [&](int64_t c, const Buf &r) {
-    Acc a = acc_identity<DT, ACC>();
+  auto accumulate = [&](Acc &a, const auto &r) {
 #pragma unroll
-    for (int i = 0; i < R; i++)
+    for (int i = 0; i < (int)(sizeof(r[0]) / sizeof(r[0][0])); i++)
 #pragma unroll
       for (int v = 0; v < V; v++)
         acc_step<DT, OP, ACC>(a, element<ESZ>(r[0][i], v), NA == 2 ? element<ESZ>(r[NA - 1][i], v) : 0u);
+  };
+  auto finish_chunk = [&](int64_t c, Acc a) {
     a = warp_tree<DT, ACC>(a);
     // two sets of slots: warp 0 reads this chunk's before it comes to the
     // next chunk's barrier, past which they are written again
@@ -410,17 +415,30 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
   if (nfull > 0) {
     Buf A, B;
     int64_t c = first;
-    load_full(c, A);
+    load_full(c, 0, A);
     while (c < nfull) {
       int64_t cn = c + gridDim.x;
-      load_full(cn, B);
-      reduce_chunk(c, A);
-      c = cn;
-      if (c >= nfull) break;
-      cn = c + gridDim.x;
-      load_full(cn, A);
-      reduce_chunk(c, B);
-      c = cn;
+      Acc a = acc_identity<DT, ACC>();
+      if constexpr (PARTS == 2) {
+        load_full(c, 1, B);
+        accumulate(a, A);
+        load_full(cn, 0, A);
+        accumulate(a, B);
+        finish_chunk(c, a);
+        c = cn;
+      } else {
+        load_full(cn, 0, B);
+        accumulate(a, A);
+        finish_chunk(c, a);
+        c = cn;
+        if (c >= nfull) break;
+        cn = c + gridDim.x;
+        load_full(cn, 0, A);
+        a = acc_identity<DT, ACC>();
+        accumulate(a, B);
+        finish_chunk(c, a);
+        c = cn;
+      }
     }
   }
   if (nfull * S < n && first == nfull % gridDim.x) {
@@ -429,7 +447,7 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
     // every lane reads the elements of the vector that n cuts (at edge)
     const int64_t e0 = nfull * S + (int64_t)w * 32 * K + (int64_t)l * V;
     const int64_t edge = n / V * V;
-    Buf r;
+    uint32_t r[NA][R][NW];
     uint32_t cut[NA][NW];
 #pragma unroll
     for (int k = 0; k < NW; k++) {
@@ -477,7 +495,9 @@ __global__ __launch_bounds__(1024) void k_reduce(const void *__restrict__ x, con
         }
       }
     }
-    reduce_chunk(nfull, r);
+    Acc a = acc_identity<DT, ACC>();
+    accumulate(a, r);
+    finish_chunk(nfull, a);
   }
   if (single) return;
 
