@@ -179,28 +179,42 @@ __device__ __forceinline__ void store_keys(uint32_t *__restrict__ p, const uint3
 }
 
 // keys of one round: U rows of 256 lane vectors starting at lane vector
-// vbase (row u = vectors vbase + 256u).  In a round that runs past n the
-// vectors past the last whole one read vector 0 instead, so that every load
-// is unconditional and all are in flight together (element by element, each
-// waited for, such a round took 1.5 us of a call on 2^22 + 17 keys); they
-// become the maximum key, and the partial vector is read element by element
+// vbase (row u = vectors vbase + 256u).  A round that runs past n reads element
+// by element, the last element in place of those past n, so that every load is
+// unconditional and all are in flight together (each waited for, such a round
+// took 1.5 us of a call on 2^22 + 17 keys); keys past n become the maximum key.
+// Full rounds have loads of their own: with the selection of addresses in them
+// 2^28 keys, one per lane, took 595 us in 32-key groups and 461 in 64-key
+// groups, 556 and 438 without.
 template <int K, int U>
 __device__ __forceinline__ void load_round(const uint32_t *keys, int64_t vbase, int64_t n, bool full,
                                            uint32_t (&key)[U][K]) {
-  const int64_t nv = full ? vbase + 256 * U : n / K;  // vectors below nv are whole
-  if (nv > 0) {
+  if (full) {
 #pragma unroll
-    for (int u = 0; u < U; u++) load_keys<K>(keys + (vbase + 256 * u < nv ? vbase + 256 * u : 0) * K, key[u]);
+    for (int u = 0; u < U; u++) load_keys<K>(keys + (vbase + 256 * u) * K, key[u]);
+    return;
   }
-  if (!full) {
+  const int64_t b0 = (vbase - threadIdx.x) * K;  // the block's first key
+  if (b0 < n) {
+    const uint32_t *src = keys + b0;
+    const uint32_t rem = (uint32_t)(n - b0);  // below 256 U K
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int64_t v = vbase + 256 * u;
-      if (v >= nv) {
+    for (int u = 0; u < U; u++)
 #pragma unroll
-        for (int r = 0; r < K; r++) key[u][r] = v == nv && v * K + r < n ? keys[v * K + r] : 0xffffffffu;
+      for (int r = 0; r < K; r++) {
+        const uint32_t o = (threadIdx.x + 256 * u) * K + r;
+        key[u][r] = src[o < rem ? o : rem - 1];
       }
-    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int r = 0; r < K; r++)
+        if ((threadIdx.x + 256 * u) * K + r >= rem) key[u][r] = 0xffffffffu;
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int r = 0; r < K; r++) key[u][r] = 0xffffffffu;
   }
 }
 
