@@ -297,8 +297,9 @@ cox_status cox_ballot_compact_away(const int32_t *x, int64_t n, int32_t *out, in
  * tile <= 256 (one key per lane; the group spans both halves of a wave,
  * exchanges across them by v_permlane32_swap, or several waves, exchanges
  * through shared memory; tile 64 is the full-wave 64-key sort), or 4 (0 = 4)
- * for tile <= 1024, which from tile 128 on names a form of its own with 32
- * keys per lane and a group inside one wave.  Other combinations give
+ * for tile <= 1024, which for long inputs (past 2^21 keys for tiles 128 and
+ * 256, 2^20 for 512 and 1024) names a form of its own with 32 keys per lane
+ * and a group inside one wave.  Other combinations give
  * COX_ERR_UNSUPPORTED.  A partial last group is sorted among its valid
  * keys.  keys, out: uint32[n] device buffers (may be the same buffer). */
 cox_status cox_tile_sort(const uint32_t *keys, uint32_t *out, int64_t n, int tile,

@@ -15,10 +15,11 @@
 //     row_half_mirror exchanges);
 //   - partner in the other half of the wave (a group of 64 lanes, the
 //     full-wave sort): the in-half exchange, then v_permlane32_swap;
-//   - partner in another wave (one key per lane, groups wider than a wave):
-//     through shared memory, between two block barriers.
-// Groups of 128 .. 1024 keys at the default 4 keys per lane are sorted by
-// k_group_sort instead (below): 32 keys per lane, a group inside one wave.
+//   - partner in another wave (groups wider than a wave): through shared
+//     memory, between two block barriers.
+// Longer inputs in groups of 128 .. 1024 keys at the default 4 keys per lane are
+// sorted by k_group_sort instead (below): 32 keys per lane, a group inside one
+// wave.
 // The layers inside one lane's K registers (every merge size up to K) are
 // replaced by Batcher's odd-even merge sort of the K registers, which needs
 // fewer comparators.  The sorted result is the unique ascending order, so
@@ -568,7 +569,7 @@ __global__ __launch_bounds__(256) void k_tile_sort_kv(const uint32_t *keys, cons
 }
 
 using sort_fn = void (*)(const uint32_t *, uint32_t *, int64_t);
-static sort_fn pick_sort(int k, int tile) {
+static sort_fn pick_sort(int k, int tile, bool wide) {
   if (tile == 32) {
     switch (k) {
     case 1: return k_tile_sort<1, 32>;
@@ -586,10 +587,10 @@ static sort_fn pick_sort(int k, int tile) {
   } else if (k == 4) {
     switch (tile) {
     case 64: return k_tile_sort<4, 64>;
-    case 128: return k_group_sort<128>;
-    case 256: return k_group_sort<256>;
-    case 512: return k_group_sort<512>;
-    case 1024: return k_group_sort<1024>;
+    case 128: return wide ? k_group_sort<128> : k_tile_sort<4, 128>;
+    case 256: return wide ? k_group_sort<256> : k_tile_sort<4, 256>;
+    case 512: return wide ? k_group_sort<512> : k_tile_sort<4, 512>;
+    case 1024: return wide ? k_group_sort<1024> : k_tile_sort<4, 1024>;
     }
   }
   return nullptr;
@@ -610,12 +611,21 @@ static sort_kv_fn pick_sort_kv(int k) {
 
 using namespace cox;
 
+// Keys past which k_group_sort takes groups of 128 .. 1024 keys at four keys a
+// lane.  It has a quarter of k_tile_sort's waves, each with four times the work,
+// so up to here its one round takes longer (us per call, k_tile_sort /
+// k_group_sort: 65,536 keys in groups of 128 / 1024 4.7 and 5.5 / 7.3 and 8.7; 2^20
+// 5.2 and 6.2 / 7.9 and 9.1; 2^21 in groups of 128 / 256 / 512 / 1024 6.4 and 6.6 /
+// 7.2 and 7.5 / 8.6 and 8.4 / 10.2 and 9.4; 3 x 2^20 7.7 and 7.5 / 9.5 and 8.9).
+static int64_t wide_min(int tile) { return tile <= 256 ? 1 << 21 : 1 << 20; }
+
 extern "C" cox_status cox_tile_sort(const uint32_t *keys, uint32_t *out, int64_t n, int tile,
                                     const cox_cfg *cfg, void *stream) {
   if (n < 0 || tile < 32 || tile > 1024 || (tile & (tile - 1))) return COX_ERR_INVALID;
   const int k = (cfg && cfg->items_per_lane) ? cfg->items_per_lane : 4;
   if (cfg && cfg->grid_blocks < 0) return COX_ERR_INVALID;
-  sort_fn fn = pick_sort(k, tile);
+  const bool wide = k == 4 && tile >= 128 && n > wide_min(tile);
+  sort_fn fn = pick_sort(k, tile, wide);
   if (!fn) return k > 0 && k <= 32 && (k & (k - 1)) == 0 ? COX_ERR_UNSUPPORTED : COX_ERR_INVALID;
   if (n == 0) return COX_OK;
   if (!keys || !out) return COX_ERR_INVALID;
@@ -623,7 +633,7 @@ extern "C" cox_status cox_tile_sort(const uint32_t *keys, uint32_t *out, int64_t
   const int64_t nvec = (n + k - 1) / k;
   const int U = k >= 16 ? 1 : 16 / k > 4 ? 4 : 16 / k;
   const int32_t want = cfg ? cfg->grid_blocks : 0;
-  if (k == 4 && tile >= 128) {
+  if (wide) {
     // k_group_sort: a block per 8192 keys, all of them launched (2^26 keys
     // in 1024-key groups: 128 us, 137 with a grid that fills the device)
     const int64_t items = (n + 8191) / 8192, most = want ? want : 0x7fffffff;
@@ -634,8 +644,7 @@ extern "C" cox_status cox_tile_sort(const uint32_t *keys, uint32_t *out, int64_t
   // default blocks per compute unit (measured at 2^28 keys): two for
   // 32-key groups and for 64-key groups with several keys per lane; six
   // for 64 keys over a full wave (0.420 ms against 0.434 with eight); eight
-  // for the other one-key forms, whose longer networks need more waves in
-  // flight.  Where two would take more than one round and six do not, all
+  // for wider groups, whose longer networks need more waves in flight.  Where two would take more than one round and six do not, all
   // rounds are launched at once: 2^22 + 17 keys in 32-key groups 7.5 us
   // against 9.8, in 64-key groups 8.2 against 11.4 (past that, two: 2^23
   // keys 14.9 us against 15.3 with six, 2^28 355 against 380).
