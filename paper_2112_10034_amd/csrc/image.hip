@@ -10,8 +10,9 @@
 //                (colsum[b][x]), row sums (rowsum[s][y]) and the tile total
 //                (total[b][s]);
 //   k_ii_colscan per column: colsum[b][x] replaced by its exclusive prefix
-//                over the bands above, T[b][x] (8 waves per 64 columns; with
-//                few bands k_ii_scan sums them itself instead);
+//                over the bands above, T[b][x], and total[b][s] likewise (8 waves
+//                per 64 columns; with few bands k_ii_scan sums them itself
+//                instead);
 //   k_ii_scan    per tile: sat[y][x] = rowprefix_x(T[b][.] + column sums
 //                of rows y0..y)[x] + corner + sum of L over rows y0..y,
 //                with L[y] the row sums of the segments to the left and
@@ -59,9 +60,9 @@ struct IiArgs {
   int64_t nb, ns;     // bands, segments
   uint32_t *colsum;   // [nb][W]: column sums, then their exclusive prefix T
   uint32_t *rowsum;   // [ns][H]
-  uint32_t *total;    // [nb][ns]
+  uint32_t *total;    // [nb][ns]: tile totals, then their exclusive prefix over the bands
   bool whole;         // k_ii_scan: one segment, all rows above are summed from the image
-  bool direct;        // k_ii_scan: colsum holds the bands' sums, not yet their prefix
+  bool direct;        // k_ii_scan: colsum and total hold the bands' sums, not yet their prefix
 };
 
 // Tile number of work item i: the tiles are handed out so that each XCD
@@ -330,7 +331,8 @@ __global__ __launch_bounds__(II_BT, 4) void k_ii_reduce16(IiArgs a) {
   }
 }
 
-// exclusive prefix of every column's band sums.  A block takes 64
+// exclusive prefix of every column's band sums, and of every segment's tile
+// totals (columns from the next multiple of 64 after W on).  A block takes 64
 // columns (one per lane) and batches of 8 x 16 bands: wave g loads and
 // sums bands g*16 .. g*16 + 15 of the batch, the 8 group sums meet in
 // shared memory, and every wave writes its bands' exclusive prefixes
@@ -339,15 +341,17 @@ constexpr int II_CS_WAVES = 8, II_CS_PB = 16;
 __global__ __launch_bounds__(64 * II_CS_WAVES) void k_ii_colscan(IiArgs a) {
   __shared__ uint32_t s_grp[II_CS_WAVES][64];
   const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  for (int64_t x0 = (int64_t)blockIdx.x * 64; x0 < a.W; x0 += (int64_t)gridDim.x * 64) {
-    const int64_t x = x0 + lane;
-    const bool okx = x < a.W;
+  const int64_t Wp = (a.W + 63) / 64 * 64;
+  for (int64_t x0 = (int64_t)blockIdx.x * 64; x0 < Wp + a.ns; x0 += (int64_t)gridDim.x * 64) {
+    uint32_t *const m = x0 < Wp ? a.colsum : a.total;
+    const int64_t width = x0 < Wp ? a.W : a.ns, x = (x0 < Wp ? x0 : x0 - Wp) + lane;
+    const bool okx = x < width;
     uint32_t carry = 0u;
     for (int64_t b0 = 0; b0 < a.nb; b0 += II_CS_WAVES * II_CS_PB) {
       const int64_t bg = b0 + (int64_t)g * II_CS_PB;
       uint32_t v[II_CS_PB], sum = 0u;
 #pragma unroll
-      for (int k = 0; k < II_CS_PB; k++) v[k] = okx && bg + k < a.nb ? a.colsum[(bg + k) * a.W + x] : 0u;
+      for (int k = 0; k < II_CS_PB; k++) v[k] = okx && bg + k < a.nb ? m[(bg + k) * width + x] : 0u;
 #pragma unroll
       for (int k = 0; k < II_CS_PB; k++) sum += v[k];
       s_grp[g][lane] = sum;
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(64 * II_CS_WAVES) void k_ii_colscan(IiArgs a) {
       }
 #pragma unroll
       for (int k = 0; k < II_CS_PB; k++) {
-        if (okx && bg + k < a.nb) a.colsum[(bg + k) * a.W + x] = off;
+        if (okx && bg + k < a.nb) m[(bg + k) * width + x] = off;
         off += v[k];
       }
       carry += tot;
@@ -487,14 +491,17 @@ __global__ __launch_bounds__(II_BT, 4) void k_ii_scan(IiArgs a) {
         }
       }
     }
-    // lane r: row y0 + r's sums of the segments to the left, and the totals
-    // of the tiles above and to the left
+    // lane r: row y0 + r's sums of the segments to the left; and the totals of
+    // the tiles above and to the left, lane k's those of segment k (added up
+    // tile by tile, b s of them, 32768 x 32768 pixels took 2480 us, 1305 so)
     uint32_t left = 0u, cv = 0u;
     for (int64_t k = 0; k < s; k++) {
       if (lane < rows) left += a.rowsum[k * a.H + y0 + lane];
       if (TH < II_TH && lane < over) cv += a.rowsum[k * a.H + b * II_TH + lane];
-      for (int64_t bb = lane; bb < b; bb += 64) cv += a.total[bb * a.ns + k];
+      if (TH < II_TH && a.direct && lane < b) cv += a.total[lane * a.ns + k];  // at most 40 bands
     }
+    if (TH == II_TH || !a.direct)
+      for (int64_t k = lane; k < s; k += 64) cv += a.total[b * a.ns + k];
     uint32_t corner = (uint32_t)__builtin_amdgcn_readlane((int)ii_wave_scan(cv), 63);
     const uint32_t above = ii_wave_scan(c[0] + c[1] + c[2] + c[3]);
     if (lane == 63) s_above[w] = above;
@@ -631,7 +638,7 @@ extern "C" cox_status cox_integral_image(const uint8_t *img, int64_t height, int
   if (!a.whole) {
     const int g1 = persistent_grid((const void *)reduce, II_BT, tiles, 0, 0, 8);
     hipLaunchKernelGGL(reduce, dim3(g1), dim3(II_BT), 0, hs, a);
-    const int64_t gc = (width + 63) / 64;
+    const int64_t gc = (width + 63) / 64 + (a.ns + 63) / 64;
     if (!a.direct)
       hipLaunchKernelGGL(k_ii_colscan, dim3((unsigned)(gc < 65536 ? gc : 65536)), dim3(64 * II_CS_WAVES), 0, hs, a);
   }

@@ -1,4 +1,5 @@
-"""Integral images of 1 to 3 columns in 32- and 64-row tiles, against numpy's
+"""Integral images of 1 to 3 columns in 32- and 64-row tiles, and of many bands
+and segments (the totals of the tiles above and to the left), against numpy's
 double cumsum."""
 import numpy as np
 import pytest
@@ -21,4 +22,12 @@ def check(H, W):
 @pytest.mark.parametrize("W", [1, 2, 3])
 @pytest.mark.parametrize("H", [4096, 4097, 4129, 12288, 12289, 12343, 70001])
 def test_narrow(H, W):
+    check(H, W)
+
+
+# bands x segments: more bands than a batch of the column scan, more segments
+# than lanes, in 64-row tiles and in 32-row ones with and without that scan
+@pytest.mark.parametrize("H,W", [(64 * 130 + 3, 2 * 1024 + 6), (64 * 259, 1025), (64 * 3, 66 * 1024 + 1),
+                                 (70, 66 * 1024 + 5), (64 * 41, 3000), (64 * 40 - 5, 3000), (64 * 9, 64 * 1024)])
+def test_bands_and_segments(H, W):
     check(H, W)
