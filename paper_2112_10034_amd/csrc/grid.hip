@@ -1083,9 +1083,15 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   const int64_t S = (int64_t)32 * sg.W * sg.k;
   const int64_t nch = (n + S - 1) / S;
   const int block = 32 * sg.W;
-  const int cap = std::min(blocks_per_cu(pk.coop, block), blocks_per_cu(pk.coop_res, block)) * device_cus();
+  // The largest grid on offer is what fits of both kernels; with R = 2, W = 8
+  // seven blocks per compute unit, though k_cg_res takes six (its 77 registers;
+  // held to 72 they spill in cg_near, 264 us instead of 252 for 50 iterations of
+  // 256 chunks).  A grid that does not fit k_cg_res runs on k_cg.
+  const int cus = device_cus(), res = blocks_per_cu(pk.coop_res, block);
+  const int offered = sg.k == 2 && sg.W == 8 && res < 7 ? 7 : res;
+  const int cap = std::min(blocks_per_cu(pk.coop, block), offered) * cus;
   int G = sg.G;
-  if (G == 0) G = device_cus();
+  if (G == 0) G = cus;
   if (G > cap) {
     if (sg.G) return COX_ERR_INVALID;
     G = cap;
@@ -1117,12 +1123,13 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   a.state = (CgState *)(w + L.state);
   a.lds_bytes = 0;
   hipStream_t hs = (hipStream_t)stream;
-  const void *fn = G >= nch ? pk.coop_res : pk.coop;
-  if (coop && G >= nch) {
+  const bool resident = G >= nch && G <= res * cus;
+  const void *fn = resident ? pk.coop_res : pk.coop;
+  if (coop && resident) {
     // the resident kernel stages CSR rows in what shared memory the grid
     // leaves: the compute unit's share per block less the static part
     hipFuncAttributes fa;
-    const int cus = device_cus(), per_cu = (G + cus - 1) / cus;
+    const int per_cu = (G + cus - 1) / cus;
     if (hipFuncGetAttributes(&fa, fn) == hipSuccess) {
       const size_t share = device_max_lds() / (size_t)per_cu, fixed = fa.sharedSizeBytes + 512;
       const size_t dyn = share > fixed ? (share - fixed) & ~(size_t)15 : 0;

@@ -1,0 +1,42 @@
+"""The largest grids that the conjugate-gradient solver takes, in blocks per
+compute unit: what is offered is accepted, one block more is refused."""
+import numpy as np
+import pytest
+
+from paper_2112_10034_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# (rows per lane, warps per block): blocks per compute unit that are offered
+OFFERED = {(1, 8): 7, (2, 8): 7, (4, 8): 4, (8, 8): 2, (1, 16): 3, (2, 16): 3, (4, 16): 2, (8, 16): 1, (1, 32): 1,
+           (2, 32): 1, (4, 32): 1, (8, 32): 1}
+
+
+def solve(cox, torch, system, R, W, grid):
+    rp, ci, val, b = system
+    x = torch.zeros_like(b)
+    result, hist = cox.cg_solve(rp, ci, val, b, x, 4, cfg=(R, W, grid))
+    cox.workspace(cox.OP_CG, cox.F32, b.numel(), cfg=(R, W, grid)).status()
+    return x, result, hist
+
+
+def tridiagonal(torch, n):
+    return [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in inputs.cg_tridiag(n, seed=n)]
+
+
+def largest(torch, sigma):
+    return OFFERED[sigma] * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("sigma", sorted(OFFERED))
+def test_offered_grids(sigma):
+    import torch
+
+    from paper_2112_10034_amd import cox
+
+    G, system = largest(torch, sigma), tridiagonal(torch, 100)
+    for u, v in zip(solve(cox, torch, system, *sigma, G), solve(cox, torch, system, *sigma, 0)):
+        assert torch.equal(u.view(torch.uint8), v.view(torch.uint8))
+    with pytest.raises(cox.CoxError) as e:
+        solve(cox, torch, system, *sigma, G + 1)
+    assert e.value.code == 1
