@@ -1086,7 +1086,7 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   // The largest grid on offer is what fits of both kernels; with R = 2, W = 8
   // seven blocks per compute unit, though k_cg_res takes six (its 77 registers;
   // held to 72 they spill in cg_near, 264 us instead of 252 for 50 iterations of
-  // 256 chunks).  A grid that does not fit k_cg_res runs on k_cg.
+  // 256 chunks).  What is launched has to be resident as a whole, see below.
   const int cus = device_cus(), res = blocks_per_cu(pk.coop_res, block);
   const int offered = sg.k == 2 && sg.W == 8 && res < 7 ? 7 : res;
   const int cap = std::min(blocks_per_cu(pk.coop, block), offered) * cus;
@@ -1098,6 +1098,15 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   }
   if (G > nch) G = (int)(nch > 0 ? nch : 1);
   if (G < 1) return COX_ERR_INVALID;
+  // Blocks that are resident together per compute unit: the runtime counts
+  // seven or eight waves per SIMD, but these kernels' 100 or so scalar registers
+  // and the 16 of the trap handler, out of 800, leave six (grids of seven blocks
+  // of 256 threads ended with their waits given up).  A grid that does not fit
+  // k_cg_res runs on k_cg, with fewer blocks if need be: results do not depend on
+  // it.
+  const int six = 6 * 4 * 64 / block;
+  const bool resident = G >= nch && G <= std::min(res, six) * cus;
+  if (coop && !resident) G = std::min(G, std::min(blocks_per_cu(pk.coop, block), six) * cus);
   char *w = (char *)ws;
   CgArgs a;
   a.rp = row_ptr;
@@ -1123,7 +1132,6 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
   a.state = (CgState *)(w + L.state);
   a.lds_bytes = 0;
   hipStream_t hs = (hipStream_t)stream;
-  const bool resident = G >= nch && G <= res * cus;
   const void *fn = resident ? pk.coop_res : pk.coop;
   if (coop && resident) {
     // the resident kernel stages CSR rows in what shared memory the grid
@@ -1131,7 +1139,9 @@ static cox_status cg_run(const int32_t *row_ptr, const int32_t *col_idx, const f
     hipFuncAttributes fa;
     const int per_cu = (G + cus - 1) / cus;
     if (hipFuncGetAttributes(&fa, fn) == hipSuccess) {
-      const size_t share = device_max_lds() / (size_t)per_cu, fixed = fa.sharedSizeBytes + 512;
+      // in the units of 1280 bytes in which it is handed out: three blocks with
+      // a third each, rounded up, were not resident together
+      const size_t share = device_max_lds() / (size_t)per_cu / 1280 * 1280, fixed = fa.sharedSizeBytes + 512;
       const size_t dyn = share > fixed ? (share - fixed) & ~(size_t)15 : 0;
       if (dyn >= (size_t)S * 4 + 1024 &&
           (dyn <= 65536 ||

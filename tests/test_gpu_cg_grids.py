@@ -1,5 +1,6 @@
 """The largest grids that the conjugate-gradient solver takes, in blocks per
-compute unit: what is offered is accepted, one block more is refused."""
+compute unit: what is offered is accepted and solves systems with a chunk per
+block, one block more is refused."""
 import numpy as np
 import pytest
 
@@ -40,3 +41,19 @@ def test_offered_grids(sigma):
     with pytest.raises(cox.CoxError) as e:
         solve(cox, torch, system, *sigma, G + 1)
     assert e.value.code == 1
+
+
+@pytest.mark.parametrize("sigma", sorted(OFFERED))
+def test_offered_grids_are_resident(sigma):
+    """A chunk per block, and some chunks more; a block that were not resident
+    would leave the others waiting until they give up."""
+    import torch
+
+    from paper_2112_10034_amd import cox
+
+    R, W = sigma
+    G = largest(torch, sigma)
+    for n in (G * 32 * W * R - 5, G * 32 * W * R + 1000):
+        system = tridiagonal(torch, n)
+        for u, v in zip(solve(cox, torch, system, R, W, G), solve(cox, torch, system, R, W, 0)):
+            assert torch.equal(u.view(torch.uint8), v.view(torch.uint8)), n
