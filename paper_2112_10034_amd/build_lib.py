@@ -10,6 +10,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -69,7 +70,12 @@ def build(verbose=False, jobs=None):
     with cf.ThreadPoolExecutor(jobs) as ex:
         bind = ex.submit(_compile_bind, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        bind.result()
+        try:
+            bind.result()
+        except Exception as e:  # calls work without it, see cox.py; a stale one must not stay
+            if os.path.exists(BIND):
+                os.remove(BIND)
+            warnings.warn(f"_coxbind.so was not built: {e}")
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB + ".tmp", *objs]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -10,11 +10,13 @@ CPU fallback.  If libcox.so has not been built, loading raises.
 The ordinary calls first try the same marshalling in native code
 (csrc/bind.cpp, built as _coxbind.so): plain contiguous tensors, the default
 schedule and a cached workspace that is large enough.  It declines anything
-else, and the Python code below does the work.
+else, and the Python code below does the work; so it does, with a warning, if
+_coxbind.so has not been built or does not load.
 """
 import ctypes as C
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -112,26 +114,42 @@ _SIGS = {
 _native = None
 
 
+class _NoNative:
+    """Stands in for _coxbind.so: declines every call, so that the Python code
+    makes it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(L):
+    try:
+        spec = importlib.util.spec_from_file_location("_coxbind", _BIND_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+    except (ImportError, OSError) as e:
+        warnings.warn(f"{_BIND_PATH} does not load ({e}): calls cost some microseconds more; "
+                      "build it with __graft_entry__.build()")
+        return _NoNative()
+    native.init(*(C.cast(getattr(L, name), C.c_void_p).value for name in (
+        "cox_warp_reduce_blocks_i32", "cox_warp_reduce", "cox_warp_dot", "cox_warp_scan", "cox_ballot_compact",
+        "cox_tile_sort", "cox_tile_reduce", "cox_warp_masked", "cox_segmented", "cox_integral_image")))
+    return native
+
+
 def lib():
     """Loads libcox.so once; raises if it has not been built."""
     global _lib, _native
     if _lib is None:
-        for path in (LIB_PATH, _BIND_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError(f"{path} is missing: build it with __graft_entry__.build() "
-                                   "(there is no CPU fallback)")
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
+                               "(there is no CPU fallback)")
         L = C.CDLL(LIB_PATH)
         for name, (res, args) in _SIGS.items():
             f = getattr(L, name)
             f.restype = res
             f.argtypes = args
-        spec = importlib.util.spec_from_file_location("_coxbind", _BIND_PATH)
-        native = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(native)
-        native.init(*(C.cast(getattr(L, name), C.c_void_p).value for name in (
-            "cox_warp_reduce_blocks_i32", "cox_warp_reduce", "cox_warp_dot", "cox_warp_scan", "cox_ballot_compact",
-            "cox_tile_sort", "cox_tile_reduce", "cox_warp_masked", "cox_segmented", "cox_integral_image")))
-        _native = native
+        _native = _load_native(L)
         _lib = L
     return _lib
 
