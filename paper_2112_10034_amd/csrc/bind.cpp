@@ -53,6 +53,14 @@ bool output(PyObject *o, at::IntArrayRef sizes, at::ScalarType dt, const at::Ten
 
 void *ptr_arg(PyObject *o) { return PyLong_AsVoidPtr(o); }
 int64_t int_arg(PyObject *o) { return PyLong_AsLongLong(o); }
+// a caller's own number; false: not a C int (as ctypes takes it), not handled here
+bool user_int(PyObject *o, int &v) {
+  int over = 0;
+  const long long w = PyLong_AsLongLongAndOverflow(o, &over);
+  if (PyErr_Occurred()) PyErr_Clear();
+  v = (int)w;
+  return !over && w == v;
+}
 
 // a status that is not 0, as the value the Python side raises from
 PyObject *status(cox_status s) { return PyLong_FromLong((long)s); }
@@ -175,8 +183,8 @@ PyObject *sort(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   COX_ARGS(4)
   const at::Tensor *x = tensor(a[0], at::kInt);
   at::Tensor out;
-  if (!x || !output(a[2], x->sizes(), at::kInt, *x, out)) Py_RETURN_NONE;
-  const int tile = (int)int_arg(a[1]);
+  int tile;
+  if (!x || !user_int(a[1], tile) || !output(a[2], x->sizes(), at::kInt, *x, out)) Py_RETURN_NONE;
   void *st = ptr_arg(a[3]);
   COX_CALL(r, p_sort((const uint32_t *)x->data_ptr(), (uint32_t *)out.data_ptr(), x->numel(), tile, nullptr, st));
   return THPVariable_Wrap(out);
@@ -188,13 +196,13 @@ PyObject *tile_reduce(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
   COX_ARGS(4)
   const at::Tensor *x = tensor(a[0], at::kInt);
-  const int64_t tile = int_arg(a[1]);
-  if (!x || tile <= 0) Py_RETURN_NONE;
+  int tile;
+  if (!x || !user_int(a[1], tile) || tile <= 0) Py_RETURN_NONE;
   const int64_t n = x->numel();
   at::Tensor out;
   if (!output(a[2], {(n + tile - 1) / tile}, at::kInt, *x, out)) Py_RETURN_NONE;
   void *st = ptr_arg(a[3]);
-  COX_CALL(r, p_tile_reduce((const int32_t *)x->data_ptr(), n, (int)tile, (int32_t *)out.data_ptr(), st));
+  COX_CALL(r, p_tile_reduce((const int32_t *)x->data_ptr(), n, tile, (int32_t *)out.data_ptr(), st));
   return THPVariable_Wrap(out);
   END_HANDLE_TH_ERRORS
 }
@@ -204,11 +212,11 @@ PyObject *masked(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
   COX_ARGS(5)
   const at::Tensor *x = tensor(a[0], at::kInt);
-  if (!x) Py_RETURN_NONE;
+  int density;
+  if (!x || !user_int(a[1], density)) Py_RETURN_NONE;
   const int64_t n = x->numel();
   at::Tensor out, rec;
   if (!output(a[2], x->sizes(), at::kInt, *x, out) || !output(a[3], {n / 32, 4}, at::kInt, *x, rec)) Py_RETURN_NONE;
-  const int density = (int)int_arg(a[1]);
   void *st = ptr_arg(a[4]);
   COX_CALL(r, p_masked((const int32_t *)x->data_ptr(), n, density, (int32_t *)out.data_ptr(),
                        (uint32_t *)rec.data_ptr(), st));
@@ -224,8 +232,8 @@ PyObject *segmented(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   const at::ScalarType dt = THPVariable_Unpack(a[0]).scalar_type();
   if (dt != at::kInt && dt != at::kFloat) Py_RETURN_NONE;
   const at::Tensor *x = tensor(a[0], dt), *off = tensor(a[1], at::kLong);
-  const int64_t which = int_arg(a[2]);
-  if (!x || !off || off->numel() < 1 || which <= 0 || which > 7) Py_RETURN_NONE;
+  int which;
+  if (!x || !off || off->numel() < 1 || !user_int(a[2], which) || which <= 0 || which > 7) Py_RETURN_NONE;
   const int64_t nseg = off->numel() - 1, n = x->numel();
   // an output that was not asked for stays what the caller gave
   at::Tensor total, y, out, count;
@@ -245,7 +253,7 @@ PyObject *segmented(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   void *ws = ptr_arg(a[7]), *st = ptr_arg(a[9]);
   const size_t wsb = (size_t)int_arg(a[8]);
   COX_CALL(r, p_segmented(x->data_ptr(), dt == at::kInt ? COX_I32 : COX_F32, (const int64_t *)off->data_ptr(), nseg, n,
-                          data(total), data(y), data(out), (int64_t *)data(count), (int)which, nullptr, ws, wsb, st));
+                          data(total), data(y), data(out), (int64_t *)data(count), which, nullptr, ws, wsb, st));
   return pack({total, y, out, count});
   END_HANDLE_TH_ERRORS
 }
