@@ -174,18 +174,23 @@ cox_status cox_tile_vote(const int32_t *pred, int64_t n, int tile, uint32_t *bal
  * 256-thread block, the SDK reduction kernels of Table 1).
  * ------------------------------------------------------------------- */
 
-/* 256-thread blocks of 8 logical warps, one element per thread:
- *   block_sums[b] = wrap32 sum of x[256b .. 256b+255] (shfl_down tree per
- *                   warp, shared-memory combine of the 8 warp values);
+/* What 256-thread blocks of 8 logical warps, one element per thread, give:
+ *   block_sums[b] = wrap32 sum of x[256b .. 256b+255] (a shfl_down tree per
+ *                   warp, then one over the 8 warp values);
  *   warp_pos_count[g] = popc(__ballot_sync(FULL, x > 0)) over
  *                   x[32g .. 32g+31].
- * Elements past n count as 0 and as not positive.
+ * Sums modulo 2^32 do not depend on the order, so a wave takes two groups of
+ * 256 elements in 16-byte loads and adds by lane shifts.  Elements past n count
+ * as 0 and as not positive.  Any 4-byte alignment.
  * x: int32[n]; block_sums: int32[ceil(n/256)];
  * warp_pos_count: int32[ceil(n/32)]; device buffers. */
 cox_status cox_warp_reduce_blocks_i32(const int32_t *x, int64_t n, int32_t *block_sums,
                                       int32_t *warp_pos_count, void *stream);
 
-/* Chunked sum of x under schedule cfg (see cox_cfg): the warp-shuffle
+/* Chunked sum of x under schedule cfg (see cox_cfg), in one launch whose last
+ * block combines the chunk partials when all have come; if some block has not
+ * run for long (another stream's kernel), the block whose partial comes last
+ * does, with the same result.  Per chunk: the warp-shuffle
  * reduction of Code 1 (Sec. 2.3) inside every block, as in the SDK
  * reduction kernels reduce4-6 / reduce / reduceFinal of Table 1, with the
  * compensated variant and the FP64 final combine of this library (the
@@ -233,9 +238,13 @@ cox_status cox_warp_reduce_away(const void *x, const void *y, cox_dtype dtype, i
  * shfl_scan_test and uniform_add kernels Table 1 lists; shfl_up is one of
  * the warp shuffles of Sec. 2.2.1), y_i = (x_0 + ... + x_i) mod 2^32, in
  * one pass: warp scans with shfl_up (Kogge-Stone), warp totals combined in
- * shared memory (the block-level carry that uniform_add applies), chunks chained by decoupled look-back (status words published
- * with device-scope atomics; chunk order from a ticket counter so that a
- * chunk only waits for chunks already being processed).  x, y: int32[n]
+ * shared memory (the block-level carry that uniform_add applies), chunk totals
+ * published with device-scope atomics.  Under the default schedule up to 2^23
+ * elements, with x and y apart, every block is one chunk and reads the totals of
+ * all chunks before it; it adds up one that does not come for some hundred
+ * microseconds from x itself.  Otherwise chunks are chained by decoupled
+ * look-back, in the order of a ticket counter, so that a chunk only waits for
+ * chunks already being processed.  x, y: int32[n]
  * device buffers (may not overlap); ws: cox_workspace_bytes(COX_OP_SCAN). */
 cox_status cox_warp_scan(const int32_t *x, int32_t *y, int64_t n, const cox_cfg *cfg, void *ws,
                          size_t ws_bytes, void *stream);
@@ -272,7 +281,8 @@ cox_status cox_warp_scan_noalloc(const int32_t *x, int32_t *y, int64_t n, const 
  * out[0 .. *count) = the kept elements in input order; *count (device int64) = their number.  Per warp and row
  * the ranks come from ballots: rank = popc(ballot & lanemask_lt) summed
  * over the lane's vector slots; warp counts are scanned in shared memory
- * and chunk offsets chained by decoupled look-back.  x: int32[n]; out:
+ * and chunk offsets found as cox_warp_scan finds its carries (one chunk per
+ * block up to 2^24 elements).  x: int32[n]; out:
  * int32[n] capacity; ws: cox_workspace_bytes(COX_OP_COMPACT). */
 cox_status cox_ballot_compact(const int32_t *x, int64_t n, int32_t *out, int64_t *count,
                               const cox_cfg *cfg, void *ws, size_t ws_bytes, void *stream);
@@ -461,10 +471,13 @@ cox_status cox_plan_destroy(cox_plan plan);
  *     sat[y][x] = sum of img[y'][x'] over y' <= y and x' <= x   (mod 2^32)
  * img: device uint8[height][width], row-major; sat: device
  * uint32[height][width].  Tiles of 64 rows x 1024 columns are reduced
- * (column sums, row sums, tile totals), the column sums are scanned down
- * the bands, and every tile is then scanned row by row (a shuffle scan of
- * 256 columns per wave and row) with its carries from above and from the left: three
- * launches, about 6.1 bytes per pixel.  The result is exact (uint32
+ * (column sums, row sums, tile totals), column sums and totals are scanned
+ * down the bands, and every tile is then scanned row by row (a shuffle scan of
+ * 256 columns per wave and row) with its carries from above and from the left:
+ * three launches, about 6.1 bytes per pixel.  Images of up to 192 such tiles
+ * are scanned in tiles of 32 or 16 rows, which read the rows of their band above
+ * them again; up to 40 bands of them need no second launch, and one segment of
+ * up to 256 rows is scanned in one launch alone.  The result is exact (uint32
  * arithmetic).  Any shape and alignment (sat 4-byte) uses vector loads and
  * stores; aligned ones for widths that are multiples of 16 (tile sums) and 4
  * (tile scans).  ws: cox_workspace_bytes(COX_OP_INTEGRAL_IMAGE,
@@ -546,7 +559,9 @@ cox_status cox_grid_exchange_absent(int32_t grid_blocks, int32_t rounds, int32_t
  * of the inner products, as tagged words, without grid barriers.
  * cfg: items_per_lane 1, 2, 4 or 8, warps_per_block 8, 16 or 32
  * (COX_ERR_UNSUPPORTED otherwise), grid_blocks 0 = one block per compute
- * unit.  Malformed CSR (indices out of range) gives meaningless results
+ * unit, COX_ERR_INVALID above what the device can be asked for; a grid that
+ * would not be resident as a whole is launched with fewer blocks (results do
+ * not depend on their number).  Malformed CSR (indices out of range) gives meaningless results
  * but no access outside the arrays.  n < 2^31 - 2^13, nnz < 2^31.
  * ws: cox_workspace_bytes(COX_OP_CG, COX_F32, n, 0, cfg). */
 cox_status cox_cg_solve(const int32_t *row_ptr, const int32_t *col_idx, const float *val, int64_t n, int64_t nnz,
