@@ -82,7 +82,14 @@ PyObject *pack(std::initializer_list<at::Tensor> ts) {
   return r;
 }
 
-// the C call without the interpreter's lock, as ctypes makes it
+// the data of a tensor, or of none.  Throws for a tensor without storage (inside a
+// vmap or grad transform), so the pointers are taken before COX_CALL gives up the
+// lock that raising needs.
+template <class T>
+T *data(const at::Tensor &t) { return t.defined() ? (T *)t.data_ptr() : nullptr; }
+
+// the C call without the interpreter's lock, as ctypes makes it; nothing in it
+// may throw
 #define COX_CALL(r, call)    \
   cox_status r;              \
   Py_BEGIN_ALLOW_THREADS;    \
@@ -107,7 +114,9 @@ PyObject *reduce_blocks(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   if (!output(a[1], {(n + 255) / 256}, at::kInt, *x, sums) || !output(a[2], {(n + 31) / 32}, at::kInt, *x, pos))
     Py_RETURN_NONE;
   void *st = ptr_arg(a[3]);
-  COX_CALL(r, p_reduce_blocks((const int32_t *)x->data_ptr(), n, (int32_t *)sums.data_ptr(), (int32_t *)pos.data_ptr(), st));
+  const int32_t *xp = data<int32_t>(*x);
+  int32_t *sp = data<int32_t>(sums), *pp = data<int32_t>(pos);
+  COX_CALL(r, p_reduce_blocks(xp, n, sp, pp, st));
   return pack({sums, pos});
   END_HANDLE_TH_ERRORS
 }
@@ -137,12 +146,12 @@ PyObject *reduce(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
     const at::ScalarType pt = y || dt != at::kInt ? at::kFloat : at::kInt;
     part = acc == COX_ACC_TWOSUM ? make({nch, 2}, pt, *x) : make({nch}, pt, *x);
   }
-  void *pp = part.defined() ? part.data_ptr() : nullptr;
+  const void *xp = data<void>(*x), *yp = y ? data<void>(*y) : nullptr;
+  void *pp = data<void>(part), *tp = data<void>(total);
   if (y) {
-    COX_CALL(r, p_dot(x->data_ptr(), y->data_ptr(), code, n, (cox_acc)acc, nullptr, pp, (double *)total.data_ptr(), ws,
-                      wsb, st));
+    COX_CALL(r, p_dot(xp, yp, code, n, (cox_acc)acc, nullptr, pp, (double *)tp, ws, wsb, st));
   } else {
-    COX_CALL(r, p_reduce(x->data_ptr(), code, n, (cox_acc)acc, nullptr, pp, total.data_ptr(), ws, wsb, st));
+    COX_CALL(r, p_reduce(xp, code, n, (cox_acc)acc, nullptr, pp, tp, ws, wsb, st));
   }
   return pack({total, part});
   END_HANDLE_TH_ERRORS
@@ -157,7 +166,10 @@ PyObject *scan(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   if (!x || !output(a[1], x->sizes(), at::kInt, *x, y)) Py_RETURN_NONE;
   void *ws = ptr_arg(a[2]), *st = ptr_arg(a[4]);
   const size_t wsb = (size_t)int_arg(a[3]);
-  COX_CALL(r, p_scan((const int32_t *)x->data_ptr(), (int32_t *)y.data_ptr(), x->numel(), nullptr, ws, wsb, st));
+  const int64_t n = x->numel();
+  const int32_t *xp = data<int32_t>(*x);
+  int32_t *yp = data<int32_t>(y);
+  COX_CALL(r, p_scan(xp, yp, n, nullptr, ws, wsb, st));
   return THPVariable_Wrap(y);
   END_HANDLE_TH_ERRORS
 }
@@ -171,8 +183,11 @@ PyObject *compact(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   if (!x || !output(a[1], x->sizes(), at::kInt, *x, out) || !output(a[2], {1}, at::kLong, *x, count)) Py_RETURN_NONE;
   void *ws = ptr_arg(a[3]), *st = ptr_arg(a[5]);
   const size_t wsb = (size_t)int_arg(a[4]);
-  COX_CALL(r, p_compact((const int32_t *)x->data_ptr(), x->numel(), (int32_t *)out.data_ptr(),
-                        (int64_t *)count.data_ptr(), nullptr, ws, wsb, st));
+  const int64_t n = x->numel();
+  const int32_t *xp = data<int32_t>(*x);
+  int32_t *op = data<int32_t>(out);
+  int64_t *cp = data<int64_t>(count);
+  COX_CALL(r, p_compact(xp, n, op, cp, nullptr, ws, wsb, st));
   return pack({out, count});
   END_HANDLE_TH_ERRORS
 }
@@ -186,7 +201,10 @@ PyObject *sort(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   int tile;
   if (!x || !user_int(a[1], tile) || !output(a[2], x->sizes(), at::kInt, *x, out)) Py_RETURN_NONE;
   void *st = ptr_arg(a[3]);
-  COX_CALL(r, p_sort((const uint32_t *)x->data_ptr(), (uint32_t *)out.data_ptr(), x->numel(), tile, nullptr, st));
+  const int64_t n = x->numel();
+  const uint32_t *xp = data<uint32_t>(*x);
+  uint32_t *op = data<uint32_t>(out);
+  COX_CALL(r, p_sort(xp, op, n, tile, nullptr, st));
   return THPVariable_Wrap(out);
   END_HANDLE_TH_ERRORS
 }
@@ -202,7 +220,9 @@ PyObject *tile_reduce(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   at::Tensor out;
   if (!output(a[2], {(n + tile - 1) / tile}, at::kInt, *x, out)) Py_RETURN_NONE;
   void *st = ptr_arg(a[3]);
-  COX_CALL(r, p_tile_reduce((const int32_t *)x->data_ptr(), n, tile, (int32_t *)out.data_ptr(), st));
+  const int32_t *xp = data<int32_t>(*x);
+  int32_t *op = data<int32_t>(out);
+  COX_CALL(r, p_tile_reduce(xp, n, tile, op, st));
   return THPVariable_Wrap(out);
   END_HANDLE_TH_ERRORS
 }
@@ -218,8 +238,10 @@ PyObject *masked(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   at::Tensor out, rec;
   if (!output(a[2], x->sizes(), at::kInt, *x, out) || !output(a[3], {n / 32, 4}, at::kInt, *x, rec)) Py_RETURN_NONE;
   void *st = ptr_arg(a[4]);
-  COX_CALL(r, p_masked((const int32_t *)x->data_ptr(), n, density, (int32_t *)out.data_ptr(),
-                       (uint32_t *)rec.data_ptr(), st));
+  const int32_t *xp = data<int32_t>(*x);
+  int32_t *op = data<int32_t>(out);
+  uint32_t *rp = data<uint32_t>(rec);
+  COX_CALL(r, p_masked(xp, n, density, op, rp, st));
   return pack({out, rec});
   END_HANDLE_TH_ERRORS
 }
@@ -249,11 +271,14 @@ PyObject *segmented(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   if ((which & 2) && !y.defined()) y = make(x->sizes(), dt, *x);
   if ((which & 4) && !out.defined()) out = at::zeros(x->sizes(), x->options().requires_grad(false));
   if ((which & 4) && !count.defined()) count = make({nseg}, at::kLong, *x);
-  auto data = [](const at::Tensor &t) -> void * { return t.defined() ? t.data_ptr() : nullptr; };
   void *ws = ptr_arg(a[7]), *st = ptr_arg(a[9]);
   const size_t wsb = (size_t)int_arg(a[8]);
-  COX_CALL(r, p_segmented(x->data_ptr(), dt == at::kInt ? COX_I32 : COX_F32, (const int64_t *)off->data_ptr(), nseg, n,
-                          data(total), data(y), data(out), (int64_t *)data(count), which, nullptr, ws, wsb, st));
+  const void *xp = data<void>(*x);
+  const int64_t *ofp = data<int64_t>(*off);
+  void *tp = data<void>(total), *yp = data<void>(y), *op = data<void>(out);
+  int64_t *cp = data<int64_t>(count);
+  COX_CALL(r, p_segmented(xp, dt == at::kInt ? COX_I32 : COX_F32, ofp, nseg, n, tp, yp, op, cp, which, nullptr, ws, wsb,
+                          st));
   return pack({total, y, out, count});
   END_HANDLE_TH_ERRORS
 }
@@ -267,8 +292,10 @@ PyObject *image(PyObject *, PyObject *const *a, Py_ssize_t n_args) {
   if (!img || img->dim() != 2 || !output(a[1], img->sizes(), at::kInt, *img, out)) Py_RETURN_NONE;
   void *ws = ptr_arg(a[2]), *st = ptr_arg(a[4]);
   const size_t wsb = (size_t)int_arg(a[3]);
-  COX_CALL(r, p_image((const uint8_t *)img->data_ptr(), img->size(0), img->size(1), (uint32_t *)out.data_ptr(), ws, wsb,
-                      st));
+  const int64_t H = img->size(0), W = img->size(1);
+  const uint8_t *ip = data<uint8_t>(*img);
+  uint32_t *op = data<uint32_t>(out);
+  COX_CALL(r, p_image(ip, H, W, op, ws, wsb, st));
   return THPVariable_Wrap(out);
   END_HANDLE_TH_ERRORS
 }
