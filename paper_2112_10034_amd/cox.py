@@ -691,8 +691,8 @@ def segmented(x, offsets, which=7, cfg=None, seg_total=None, y=None, out=None, s
     nseg + 1 entries) in one fused launch.  Returns (seg_total, y, out,
     seg_count) with None for outputs not selected by `which`."""
     ws = _cached_ws(OP_SEGMENTED, x)
-    if cfg is None and ws is not None:
-        r = _native.segmented(x, offsets, int(which), seg_total, y, out, seg_count, ws.ptr, ws.nbytes, _stream())
+    if cfg is None and ws is not None and type(which) is int:
+        r = _native.segmented(x, offsets, which, seg_total, y, out, seg_count, ws.ptr, ws.nbytes, _stream())
         if _done(r, "cox_segmented"):
             return r
     _need(offsets, torch.int64, "offsets")

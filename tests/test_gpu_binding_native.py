@@ -64,3 +64,14 @@ def test_numbers_past_a_c_int(dev):
             cox.tile_sort(x, bad + 1)
         with pytest.raises(cox.CoxError):
             cox.warp_masked(x, bad * 4 - 1)
+
+
+def test_an_output_selection_that_is_no_int(dev):
+    torch, cox = dev
+    x = torch.arange(4096, dtype=torch.int32, device="cuda")
+    off = torch.tensor([0, 4096], device="cuda")
+    cox.segmented(x, off)
+    for which in (2.0, "2", None):
+        with pytest.raises(TypeError):
+            cox.segmented(x, off, which)
+    assert cox.segmented(x, off, True)[1] is None
